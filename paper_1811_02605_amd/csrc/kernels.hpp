@@ -61,7 +61,7 @@ struct Ctl {
     int32_t conv_iter; // iteration index at which flag was set
     int32_t check;     // mode 0: the next iteration kernel forms ||W r||^2
     int32_t check_every;  // mode 0: a check at least every check_every iterations
-    int32_t pad;
+    int32_t launches;  // PC2: direction launches that did work
 };
 
 enum { FLAG_RUN = 0, FLAG_CONV = 1, FLAG_MAXIT = 2, FLAG_BREAK = -2 };
@@ -1160,6 +1160,7 @@ __global__ void k_ctl_init(Ctl *ctl, int mode, int iter0, int max_iter, double t
     ctl->conv_iter = -1;
     ctl->check = check0;
     ctl->check_every = check_every > 0 ? check_every : 1;
+    ctl->launches = 0;
 }
 
 // ---------------------------------------------------------------- simple stencil tiles

@@ -1061,181 +1061,56 @@ static int64_t pc2_blocks(const Shape &s, int *nbi, int *nbj, int *nbk) {
     return (int64_t)*nbi * *nbj * *nbk;
 }
 
-// PCG with the block-Jacobi ILU(0) preconditioner on the scaled system, from
-// x (scaled) and r = b^ - A^ x already in r.  Iterations are counted from
-// iter0; the run stops on ||W r||^2 <= tol2 (every iteration), at max_iter
-// or on a breakdown.  The modified diagonal must already be in d.
-// PC2 solve: rows of loads in flight ahead of the scan.  Measured at one
-// fixed placement on the 256 x 320 x 640 grid: two rows 1.2% faster than one
-// in double precision (2007 vs 2031 us per PC2 iteration), no gain in single
-// precision.
-#ifndef MAS_PC2_PF64
-#define MAS_PC2_PF64 2
-#endif
-#ifndef MAS_PC2_PF32
-#define MAS_PC2_PF32 1
-#endif
-template <typename T>
-static constexpr int pc2_prefetch() {
-    return std::is_same<T, float>::value ? MAS_PC2_PF32 : MAS_PC2_PF64;
-}
-
-template <typename T>
-static int run_pcg_pc2(Ctx &cx, T *r, T *z, T *const p[2], T *q, T *d, T *x, int iter0,
-                       int max_iter, double tol2, PcgResult *res) {
-    const mas_op *op = cx.op;
-    const Shape &s = op->s;
-    hipStream_t st = cx.stream;
-    int nbi, nbj, nbk;
-    const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
-    const T *cc[3];
-    if constexpr (std::is_same<T, float>::value) {
-        for (int t = 0; t < 3; ++t) cc[t] = op->c32[t];
-    } else {
-        for (int t = 0; t < 3; ++t) cc[t] = op->c64[t];
-    }
-    hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, cx.ctl, 0, iter0, max_iter, tol2, 0.0,
-                       (int)FLAG_RUN, 0, 1);
-    Pc2Args<T> a{cc[0], cc[1], cc[2], op->w, d, r, x, z, q, nullptr, cx.partials,
-                 cx.ctl, s.dims(), nbi, nbj, nbk, 0};
-    // z = M^-1 r of the initial residual, (r, z), the stopping test
-    hipLaunchKernelGGL((k_pc2_solve<T, pc2_prefetch<T>()>), dim3((unsigned)nb), dim3(kWave), 0, st, a);
-    hipLaunchKernelGGL(k_pc2_fin_b, dim3(1), dim3(kRedThreads), 0, st, cx.partials, (int)nb, cx.ctl, 1);
-    LAUNCHCHK();
-    FlagPoll poll(cx);
-    int e = poll.init();
-    if (e != MAS_OK) return e;
-    // the direction and SpMV step: the PCG iteration kernel with no r, q or
-    // x (p = z + beta p, q = A^ p, partial (p, q) first of each block's kNV)
-    IterArgs<T> it{};
-    it.cr = cc[0];
-    it.ct = cc[1];
-    it.cp = cc[2];
-    it.w = op->w;
-    it.partials = cx.partials;
-    it.ctl = cx.ctl;
-    it.d = s.dims();
-    const int V = iter_vec<T>(s.np, 1);
-    it.tiles_i = s.tiles_i(V, cx.chunk);
-    it.tiles_k = s.tiles_k(V);
-    it.tiles_j = s.tiles_j();
-    it.ti = s.ti(V, cx.chunk);
-    it.nblk = (int)s.nblk_iter(V, cx.chunk);
-    it.records = 0;
-    constexpr int VW = vec_full<T>();
-    const dim3 igrid((unsigned)it.nblk), iblock(kWave * kTJ);
-    a.update = 1;
-    int k = iter0;
-    bool stop = false;
-    while (!stop && k < max_iter) {
-        const int kend = std::min(max_iter, k + 16);
-        for (; k < kend; ++k) {
-            // the first direction is z itself (beta = 0): p_old points at z
-            const T *p_old = (k == iter0) ? z : p[k & 1];
-            T *p_new = p[(k + 1) & 1];
-            const bool sample = cx.timing && (k % 16 == 7) && cx.ev.size() < 128;
-            if (sample) {
-                hipEvent_t e0, e1;
-                HIPCHK(hipEventCreate(&e0));
-                HIPCHK(hipEventCreate(&e1));
-                cx.ev.push_back(e0);
-                cx.ev.push_back(e1);
-                cx.ev_iter.push_back(k + 1);
-                HIPCHK(hipEventRecord(e0, st));
-            }
-            it.r_in[0] = z;
-            it.p_in[0] = p_old;
-            it.p_out[0] = p_new;
-            it.q_out[0] = q;
-            if (V == VW)
-                hipLaunchKernelGGL((k_pcg_iter<T, 1, kTJ, kRPW, VW, false>), igrid, iblock,
-                                   0, st, it);
-            else
-                hipLaunchKernelGGL((k_pcg_iter<T, 1, kTJ, kRPW, 1, false>), igrid, iblock,
-                                   0, st, it);
-            hipLaunchKernelGGL(k_pc2_fin_a, dim3(1), dim3(kRedThreads), 0, st, cx.partials, it.nblk,
-                               (int)kNV, cx.ctl);
-            a.p = p_new;
-            hipLaunchKernelGGL((k_pc2_solve<T, pc2_prefetch<T>()>), dim3((unsigned)nb), dim3(kWave), 0, st, a);
-            hipLaunchKernelGGL(k_pc2_fin_b, dim3(1), dim3(kRedThreads), 0, st, cx.partials, (int)nb,
-                               cx.ctl, 0);
-            if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
-        }
-        LAUNCHCHK();
-        e = poll.after_batch(1, &stop);
-        if (e != MAS_OK) return e;
-    }
-    HIPCHK(hipStreamSynchronize(st));
-    Ctl h;
-    e = read_ctl(cx, &h);
-    if (e != MAS_OK) return e;
-    res->flag[0] = h.flag;
-    res->last_iter[0] = (h.flag == FLAG_RUN) ? max_iter : h.conv_iter;
-    return MAS_OK;
-}
-
-// PC2-PCG for NR right-hand sides under one operator (FP64): per right-hand
-// side its control block, r, z, p (two), q and x; the modified diagonal d and
-// the couplings are shared.  The direction and SpMV step of all of them is
-// one launch of the several-right-hand-side iteration kernel (couplings read
-// once); the block solves and the finalize kernels run per right-hand side.
-// Right-hand sides with active[h] false get a stopped control block and move
-// no bytes.  All start at iteration iter0.
+// The vectors of one PC2-preconditioned run of NR right-hand sides: r, z, p
+// (two) and q of each, x, and the shared modified diagonal d.
 template <typename T, int NR>
-static int run_pcg_pc2_multi(Ctx &cx, T *const r[NR], T *const z[NR], T *const p[NR][2],
-                             T *const q[NR], const T *d, T *const x[NR], const bool active[NR],
-                             const int max_iter[NR], const double tol2[NR], int iter0,
-                             PcgResult *res) {
+struct Pc2Vecs {
+    T *r[NR], *z[NR], *p[NR][2], *q[NR], *x[NR];
+    const T *d;
+};
+
+// PCG with the block-Jacobi ILU(0) preconditioner on the scaled system for NR
+// right-hand sides under one operator, from x (scaled) and r = b^ - A^ x^
+// already in v.  All start at iteration iter0; a run stops on
+// ||W r||^2 <= tol2 (every iteration), at its max_iter or on a breakdown;
+// right-hand sides with active[h] false get a stopped control block and move
+// no bytes.  An iteration is one launch of the PCG iteration kernel with no r
+// and q inputs (p = z + beta p, q = A^ p, partial (p, q) first of each block's
+// kNV, and x every second launch, two updates at a time) and one block-solve
+// launch, each carrying all right-hand sides with the operator read once.
+template <typename T, int NR>
+static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], const int max_iter[NR],
+                       const double tol2[NR], int iter0, PcgResult *res) {
     const mas_op *op = cx.op;
     const Shape &s = op->s;
     hipStream_t st = cx.stream;
     int nbi, nbj, nbk;
     const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
-    for (int h = 0; h < NR; ++h)
+    int kmax = iter0;
+    for (int h = 0; h < NR; ++h) {
         hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, cx.ctl + h, 0, iter0,
                            active[h] ? max_iter[h] : iter0, tol2[h], 0.0,
                            (int)(active[h] ? FLAG_RUN : FLAG_CONV), 0, 1);
-    // the block solves of all right-hand sides in one launch (couplings, w
-    // and d read once); right-hand side h's partials at partials + 2 h nb
+        if (active[h]) kmax = std::max(kmax, max_iter[h]);
+    }
     const T *cc[3];
     if constexpr (std::is_same<T, float>::value) {
         for (int t = 0; t < 3; ++t) cc[t] = op->c32[t];
     } else {
         for (int t = 0; t < 3; ++t) cc[t] = op->c64[t];
     }
-    Pc2MultiArgs<T, NR> a{};
+    Pc2Args<T, NR> a{};
     a.cr = cc[0];
     a.ct = cc[1];
     a.cp = cc[2];
     a.w = op->w;
-    a.d = d;
-    for (int h = 0; h < NR; ++h) {
-        a.r[h] = r[h];
-        a.x[h] = x[h];
-        a.z[h] = z[h];
-        a.q[h] = q[h];
-        a.p[h] = nullptr;
-    }
+    a.d = v.d;
     a.partials = cx.partials;
     a.ctl = cx.ctl;
     a.dm = s.dims();
     a.nbi = nbi;
     a.nbj = nbj;
     a.nbk = nbk;
-    a.update = 0;
-    auto solve_all = [&](int is_first) {
-        hipLaunchKernelGGL((k_pc2_solve_multi<T, NR>), dim3((unsigned)nb), dim3(kWave), 0, st, a);
-        for (int h = 0; h < NR; ++h)
-            hipLaunchKernelGGL(k_pc2_fin_b, dim3(1), dim3(kRedThreads), 0, st,
-                               cx.partials + 2 * h * nb, (int)nb, cx.ctl + h, is_first);
-    };
-    // z = M^-1 r of the initial residuals, (r, z), the stopping tests
-    solve_all(1);
-    a.update = 1;
-    LAUNCHCHK();
-    FlagPoll poll(cx);
-    int e = poll.init();
-    if (e != MAS_OK) return e;
     IterArgs<T> it{};
     it.cr = cc[0];
     it.ct = cc[1];
@@ -1251,11 +1126,29 @@ static int run_pcg_pc2_multi(Ctx &cx, T *const r[NR], T *const z[NR], T *const p
     it.ti = s.ti(V, cx.chunk);
     it.nblk = (int)s.nblk_iter(V, cx.chunk);
     it.records = 0;
+    for (int h = 0; h < NR; ++h) {
+        a.r[h] = v.r[h];
+        a.z[h] = v.z[h];
+        a.q[h] = v.q[h];
+        it.r_in[h] = v.z[h];
+        it.q_out[h] = v.q[h];
+        it.x[h] = v.x[h];
+    }
+    auto solve_all = [&](int is_first) {
+        a.update = is_first ? 0 : 1;
+        hipLaunchKernelGGL((k_pc2_solve<T, NR>), dim3((unsigned)nb), dim3(kPc2Threads), 0, st, a);
+        for (int h = 0; h < NR; ++h)
+            hipLaunchKernelGGL(k_pc2_fin_b, dim3(1), dim3(kRedThreads), 0, st,
+                               cx.partials + 2 * h * nb, (int)nb, cx.ctl + h, is_first);
+    };
+    // z = M^-1 r of the initial residuals, (r, z), the stopping tests
+    solve_all(1);
+    LAUNCHCHK();
+    FlagPoll poll(cx);
+    int e = poll.init();
+    if (e != MAS_OK) return e;
     constexpr int VW = vec_full<T>();
     const dim3 igrid((unsigned)it.nblk), iblock(kWave * kTJ);
-    int kmax = iter0;
-    for (int h = 0; h < NR; ++h)
-        if (active[h]) kmax = std::max(kmax, max_iter[h]);
     int k = iter0;
     bool stop = false;
     while (!stop && k < kmax) {
@@ -1273,11 +1166,10 @@ static int run_pcg_pc2_multi(Ctx &cx, T *const r[NR], T *const z[NR], T *const p
             }
             for (int h = 0; h < NR; ++h) {
                 // the first direction is z itself (beta = 0): p_old points at z
-                it.r_in[h] = z[h];
-                it.p_in[h] = (k == iter0) ? z[h] : p[h][k & 1];
-                it.p_out[h] = p[h][(k + 1) & 1];
-                it.q_out[h] = q[h];
+                it.p_in[h] = (k == iter0) ? v.z[h] : v.p[h][k & 1];
+                it.p_out[h] = v.p[h][(k + 1) & 1];
             }
+            it.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
             if (V == VW)
                 hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, VW, false>), igrid, iblock,
                                    0, st, it);
@@ -1287,13 +1179,26 @@ static int run_pcg_pc2_multi(Ctx &cx, T *const r[NR], T *const z[NR], T *const p
             for (int h = 0; h < NR; ++h)
                 hipLaunchKernelGGL(k_pc2_fin_a, dim3(1), dim3(kRedThreads), 0, st,
                                    cx.partials + h * kNV, it.nblk, (int)(NR * kNV), cx.ctl + h);
-            for (int h = 0; h < NR; ++h) a.p[h] = p[h][(k + 1) & 1];
             solve_all(0);
             if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
         }
         LAUNCHCHK();
         e = poll.after_batch(NR, &stop);
         if (e != MAS_OK) return e;
+    }
+    // the x updates the last launches left
+    {
+        CatchupArgs<T> ca{};
+        for (int h = 0; h < NR; ++h) {
+            ca.x[h] = v.x[h];
+            for (int t = 0; t < 2; ++t) ca.p[h][t] = v.p[h][t];
+        }
+        ca.ctl = cx.ctl;
+        ca.n = s.n;
+        ca.iter0 = iter0;
+        const int64_t cblk = std::min<int64_t>((s.n + 255) / 256, kCatchupBlocks);
+        hipLaunchKernelGGL(k_pc2_catchup<T>, dim3((unsigned)cblk, NR), dim3(256), 0, st, ca);
+        LAUNCHCHK();
     }
     HIPCHK(hipStreamSynchronize(st));
     for (int h = 0; h < NR; ++h) {
@@ -1406,20 +1311,21 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
         // (or a quarter of the final tolerance), then x^ += d in double and
         // r^ = b^ - A^ x^ in double.  The factor is the double-precision one,
         // rounded.
-        float *r = reinterpret_cast<float *>(base + L.vec[0][0]);
-        float *z = reinterpret_cast<float *>(base + L.vec[0][1]);
-        float *const p[2] = {reinterpret_cast<float *>(base + L.vec[0][2]),
-                             reinterpret_cast<float *>(base + L.vec[0][3])};
-        float *q = reinterpret_cast<float *>(base + L.vec[0][4]);
+        Pc2Vecs<float, 1> v{};
+        float *r = v.r[0] = reinterpret_cast<float *>(base + L.vec[0][0]);
+        v.z[0] = reinterpret_cast<float *>(base + L.vec[0][1]);
+        v.p[0][0] = reinterpret_cast<float *>(base + L.vec[0][2]);
+        v.p[0][1] = reinterpret_cast<float *>(base + L.vec[0][3]);
+        v.q[0] = reinterpret_cast<float *>(base + L.vec[0][4]);
         float *dm = reinterpret_cast<float *>(base + L.vec[0][5]);
-        float *dh = reinterpret_cast<float *>(base + L.dh[0]);
+        v.d = dm;
+        float *dh = v.x[0] = reinterpret_cast<float *>(base + L.dh[0]);
         int nbi, nbj, nbk;
         const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
         if (nb * 2 * 8 > L.bhat[0] - L.partials || s.nblk_simple() * 8 > L.bhat[0] - L.partials)
             return fail(MAS_EINVAL, "internal: partial-sum area too small for PC2");
         if (nb > INT32_MAX) return fail(MAS_EINVAL, "grid too large for PC2");
-        Pc2Args<double> fa{op->c64[0], op->c64[1], op->c64[2], op->w, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, nullptr, nullptr, cx.ctl, d, nbi, nbj, nbk, 0};
+        Pc2FacArgs fa{op->c64[0], op->c64[1], op->c64[2], d, nbi, nbj, nbk};
         hipLaunchKernelGGL(k_pc2_factor<float>, dim3((unsigned)nb), dim3(kWave), 0, cx.stream, fa, dm);
         hipLaunchKernelGGL(k_fill<float>, sgrid, sblock, 0, cx.stream, dh, d, 0.0f);
         LAUNCHCHK();
@@ -1433,7 +1339,9 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
         while (status != MAS_OK && info.outer_iters < o.max_outer && used < o.max_iters) {
             const double thr = std::max(d2 * rw2, 0.25 * tol2);
             PcgResult pr{};
-            st = run_pcg_pc2<float>(cx, r, z, p, q, dm, dh, 0, o.max_iters - used, thr, &pr);
+            const bool active[1] = {true};
+            const int maxit[1] = {o.max_iters - used};
+            st = run_pcg_pc2<float, 1>(cx, v, active, maxit, &thr, 0, &pr);
             if (st != MAS_OK) return st;
             timing_summary(cx, pr.last_iter[0], &info);
             used += pr.last_iter[0];
@@ -1456,19 +1364,21 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
         info.iters = used;
     } else if (o.precond == MAS_PC2) {
         // vectors: r, z, p[2], q, and the modified diagonal
-        double *r = reinterpret_cast<double *>(base + L.vec[0][0]);
-        double *z = reinterpret_cast<double *>(base + L.vec[0][1]);
-        double *const p[2] = {reinterpret_cast<double *>(base + L.vec[0][2]),
-                              reinterpret_cast<double *>(base + L.vec[0][3])};
-        double *q = reinterpret_cast<double *>(base + L.vec[0][4]);
+        Pc2Vecs<double, 1> v{};
+        double *r = v.r[0] = reinterpret_cast<double *>(base + L.vec[0][0]);
+        v.z[0] = reinterpret_cast<double *>(base + L.vec[0][1]);
+        v.p[0][0] = reinterpret_cast<double *>(base + L.vec[0][2]);
+        v.p[0][1] = reinterpret_cast<double *>(base + L.vec[0][3]);
+        v.q[0] = reinterpret_cast<double *>(base + L.vec[0][4]);
         double *dm = reinterpret_cast<double *>(base + L.vec[0][5]);
+        v.d = dm;
+        v.x[0] = x;
         int nbi, nbj, nbk;
         const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
         if (nb * 2 * 8 > L.bhat[0] - L.partials || s.nblk_simple() * 8 > L.bhat[0] - L.partials)
             return fail(MAS_EINVAL, "internal: partial-sum area too small for PC2");
         if (nb > INT32_MAX) return fail(MAS_EINVAL, "grid too large for PC2");
-        Pc2Args<double> fa{op->c64[0], op->c64[1], op->c64[2], op->w, dm, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, nullptr, cx.ctl, d, nbi, nbj, nbk, 0};
+        Pc2FacArgs fa{op->c64[0], op->c64[1], op->c64[2], d, nbi, nbj, nbk};
         hipLaunchKernelGGL(k_pc2_factor<double>, dim3((unsigned)nb), dim3(kWave), 0, cx.stream, fa, dm);
         LAUNCHCHK();
         double rw2 = 0.0;
@@ -1479,7 +1389,9 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
         int iter0 = 0;
         while (status != MAS_OK && iter0 < o.max_iters) {
             PcgResult pr{};
-            st = run_pcg_pc2(cx, r, z, p, q, dm, x, iter0, o.max_iters, tol2, &pr);
+            const bool active[1] = {true};
+            const int maxit[1] = {o.max_iters};
+            st = run_pcg_pc2<double, 1>(cx, v, active, maxit, &tol2, iter0, &pr);
             if (st != MAS_OK) return st;
             timing_summary(cx, pr.last_iter[0], &info);
             info.iters = pr.last_iter[0];
@@ -1741,23 +1653,23 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
     if (o.precond == MAS_PC2) {
         // vectors of right-hand side h: r, z, p (two), q; the shared modified
         // diagonal in right-hand side 0's sixth vector
-        double *r[NR], *z[NR], *p[NR][2], *q[NR], *xs[NR];
+        Pc2Vecs<double, NR> pv{};
         for (int h = 0; h < NR; ++h) {
-            r[h] = reinterpret_cast<double *>(base + L.vec[h][0]);
-            z[h] = reinterpret_cast<double *>(base + L.vec[h][1]);
-            p[h][0] = reinterpret_cast<double *>(base + L.vec[h][2]);
-            p[h][1] = reinterpret_cast<double *>(base + L.vec[h][3]);
-            q[h] = reinterpret_cast<double *>(base + L.vec[h][4]);
-            xs[h] = v.x[h];
+            pv.r[h] = reinterpret_cast<double *>(base + L.vec[h][0]);
+            pv.z[h] = reinterpret_cast<double *>(base + L.vec[h][1]);
+            pv.p[h][0] = reinterpret_cast<double *>(base + L.vec[h][2]);
+            pv.p[h][1] = reinterpret_cast<double *>(base + L.vec[h][3]);
+            pv.q[h] = reinterpret_cast<double *>(base + L.vec[h][4]);
+            pv.x[h] = v.x[h];
         }
         double *dm = reinterpret_cast<double *>(base + L.vec[0][5]);
+        pv.d = dm;
         int nbi, nbj, nbk;
         const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
         if (NR * nb * 2 * 8 > L.bhat[0] - L.partials)
             return fail(MAS_EINVAL, "internal: partial-sum area too small for PC2");
         if (nb > INT32_MAX) return fail(MAS_EINVAL, "grid too large for PC2");
-        Pc2Args<double> fa{op->c64[0], op->c64[1], op->c64[2], op->w, dm, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, nullptr, cx.ctl, d, nbi, nbj, nbk, 0};
+        Pc2FacArgs fa{op->c64[0], op->c64[1], op->c64[2], d, nbi, nbj, nbk};
         hipLaunchKernelGGL(k_pc2_factor<double>, dim3((unsigned)nb), dim3(kWave), 0, stream, fa, dm);
         LAUNCHCHK();
         int iter0 = 0, restarts = 0;
@@ -1771,7 +1683,7 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
             }
             if (!any) break;
             PcgResult pr{};
-            int st = run_pcg_pc2_multi<double, NR>(cx, r, z, p, q, dm, xs, active, maxit, v.tol2, iter0, &pr);
+            int st = run_pcg_pc2<double, NR>(cx, pv, active, maxit, v.tol2, iter0, &pr);
             if (st != MAS_OK) return st;
             int last = iter0;
             for (int h = 0; h < NR; ++h) {
@@ -1782,7 +1694,7 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
                 st = read_ctl(cx, &hc, h);
                 if (st != MAS_OK) return st;
                 info[h].rel_resid_recursive = std::sqrt(hc.rw) / bnorm[h];
-                st = residual<double>(cx, bhat[h], v.x[h], r[h], &rw2[h]);
+                st = residual<double>(cx, bhat[h], v.x[h], pv.r[h], &rw2[h]);
                 if (st != MAS_OK) return st;
                 info[h].rel_resid_true = std::sqrt(rw2[h]) / bnorm[h];
                 if (rw2[h] <= v.tol2[h]) {
@@ -1971,22 +1883,23 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
     // and q of right-hand side h in its first five vectors, the modified
     // diagonal in right-hand side 0's sixth
     float *dm = reinterpret_cast<float *>(base + L.vec[0][5]);
-    float *pr_[NR], *pz_[NR], *pp_[NR][2], *pq_[NR];
+    Pc2Vecs<float, NR> pv{};
     if (pc2) {
         for (int h = 0; h < NR; ++h) {
-            pr_[h] = v.r[h][0];
-            pz_[h] = v.r[h][1];
-            pp_[h][0] = v.p[h][0];
-            pp_[h][1] = v.p[h][1];
-            pq_[h] = v.q[h][0];
+            pv.r[h] = v.r[h][0];
+            pv.z[h] = v.r[h][1];
+            pv.p[h][0] = v.p[h][0];
+            pv.p[h][1] = v.p[h][1];
+            pv.q[h] = v.q[h][0];
+            pv.x[h] = dh[h];
         }
+        pv.d = dm;
         int nbi, nbj, nbk;
         const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
         if (NR * nb * 2 * 8 > L.bhat[0] - L.partials)
             return fail(MAS_EINVAL, "internal: partial-sum area too small for PC2");
         if (nb > INT32_MAX) return fail(MAS_EINVAL, "grid too large for PC2");
-        Pc2Args<double> fa{op->c64[0], op->c64[1], op->c64[2], op->w, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, nullptr, nullptr, cx.ctl, d, nbi, nbj, nbk, 0};
+        Pc2FacArgs fa{op->c64[0], op->c64[1], op->c64[2], d, nbi, nbj, nbk};
         hipLaunchKernelGGL(k_pc2_factor<float>, dim3((unsigned)nb), dim3(kWave), 0, stream, fa, dm);
         LAUNCHCHK();
     }
@@ -2016,8 +1929,7 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
         }
         if (!any) break;
         PcgResult pr{};
-        int st = pc2 ? run_pcg_pc2_multi<float, NR>(cx, pr_, pz_, pp_, pq_, dm, dh, active, maxit,
-                                                    thr, 0, &pr)
+        int st = pc2 ? run_pcg_pc2<float, NR>(cx, pv, active, maxit, thr, 0, &pr)
                      : run_pcg<float, NR>(cx, v, c32, 1, 0, 1, &pr);
         if (st != MAS_OK) return st;
         int last = 0;
@@ -2050,7 +1962,7 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
                 info[h].rel_resid_recursive = std::sqrt(hc.rw) / bnorm[h];
                 hipLaunchKernelGGL(k_fold, sgrid, sblock, 0, stream, dh[h], d, xh[h]);
                 LAUNCHCHK();
-                st = residual<float>(cx, bhat[h], xh[h], pr_[h], &rw2[h]);
+                st = residual<float>(cx, bhat[h], xh[h], pv.r[h], &rw2[h]);
                 if (st != MAS_OK) return st;
             } else if (reliable) {
                 // x^ += d^ + alpha_K p_K, then the double-precision residual

@@ -21,9 +21,9 @@
 // block's (r, theta) rows in order and solves each row's phi recurrence
 // d_k = s_k - c^2 / d_{k-1} by a prefix scan of 2 x 2 matrices (the maps
 // d -> (s d - c^2) / d compose as matrix products).
-// Solve: one wave per block, lane k' owns phi offset k' (coalesced rows), and
-// the wave walks the block's (r, theta) rows in order.  The r and theta
-// terms come from the rows already done (kept in registers); along phi the
+// Solve: one wave per r plane of the block, lane k' owns phi offset k'
+// (coalesced rows), the rows taken as a wavefront over (r, theta).  The r and
+// theta terms come from the rows already done; along phi the
 // forward sweep is the first-order recurrence y_k = c_k y_{k-1} + b_k with
 // c_k = c^p_{k-1,k} / d_k, solved by a prefix scan of the affine maps
 // y -> c y + b across the lanes (the backward sweep scans the other way).
@@ -36,21 +36,11 @@ namespace mas {
 constexpr int kPc2I = 8, kPc2J = 8, kPc2K = 64;
 static_assert(kPc2K == kWave, "one lane per phi offset of a block");
 
-// T: the precision of the couplings, the modified diagonal and the PCG
-// vectors (double, or float inside double-precision refinement); w and the
-// partial sums are double.
-template <typename T>
-struct Pc2Args {
-    const T *cr, *ct, *cp;       // scaled couplings to the +r, +theta, +phi neighbours
-    const double *w;
-    T *d;                        // modified diagonal (written by the factor kernel)
-    T *r, *x, *z;                // solve: r -= alpha q, x += alpha p, z = M^-1 r
-    const T *q, *p;
-    double *partials;            // [blocks][2]: (r, z), ||W r||^2
-    const Ctl *ctl;
+// The factor kernel's arguments.
+struct Pc2FacArgs {
+    const double *cr, *ct, *cp;  // scaled couplings to the +r, +theta, +phi neighbours
     Dims dm;
     int nbi, nbj, nbk;           // blocks per direction
-    int update;                  // solve: apply the alpha updates first
 };
 
 // Inclusive scan of the affine maps y -> C y + B over the 64 lanes in lane
@@ -170,7 +160,7 @@ struct Pc2FacPlane {
 };
 
 template <typename TOUT>
-__global__ __launch_bounds__(kWave) void k_pc2_factor(Pc2Args<double> a, TOUT *dout) {
+__global__ __launch_bounds__(kWave) void k_pc2_factor(Pc2FacArgs a, TOUT *dout) {
     const Dims &dm = a.dm;
     const int blk = blockIdx.x;
     const int bk = blk % a.nbk, bj = (blk / a.nbk) % a.nbj, bi = blk / (a.nbk * a.nbj);
@@ -253,375 +243,220 @@ __global__ __launch_bounds__(kWave) void k_pc2_factor(Pc2Args<double> a, TOUT *d
     }
 }
 
-// z = M^-1 r, first applying r -= alpha q and x += alpha p when a.update;
-// per-block partials (r, z) and ||W r||^2.  Each sweep loads the next row's
-// inputs before it scans the current row, so a wave keeps one row of loads
-// in flight behind its scans.
+// z = M^-1 r for NR right-hand sides, first applying r -= alpha q when
+// a.update; per-block partials (r, z) and ||W r||^2 of each (right-hand side
+// h's at partials + 2 h nblk).  A right-hand side whose control block is
+// stopped is left alone.
 // With L the strictly lower couplings and D = diag(d), M = (D - L) D^-1 (D - L^T),
 // the forward sweep gives y = (D - L)^-1 r and z = (D - L^T)^-1 D y, so
 // (r, z) = r^T (D - L^T)^-1 D (D - L)^-1 r = y^T D y: the forward sweep
 // accumulates it and the backward sweep need not read r again.
-template <typename T>
-struct Pc2Fwd {
-    T r, q, x, p;
-    double w;
-    T d, cr, ct, cp;
-};
-template <typename T>
-struct Pc2Bwd {
-    T cr, ct, d, y, cp;
+//
+// What bounds it: memory, 9 words per cell (r, q, w, d, three couplings; r and
+// z written) once nothing is read twice, and on small grids the chain of
+// dependent rows.  So the whole block sits in registers between the sweeps,
+// and the rows run as a wavefront: wave ii of the block's eight owns r plane ii
+// with all its rows in registers, loads everything up front (about 50 loads in
+// flight per wave), and works on row jj in step ii + jj, when row jj of the
+// plane below (ii - 1, through LDS) and row jj - 1 (its own) are done: 15
+// steps a sweep instead of 64, one barrier each.  Every wave passes the same
+// number of barriers: ii before its first row, one per row, ni - 1 - ii after.
+// In the backward sweep lane l takes phi offset 63 - l, so that the recurrence
+// runs up the lanes again: y, 1/d and the phi and theta couplings are turned
+// round by a lane permute, the r couplings come reversed from the LDS copy
+// that the forward sweep of the plane above read too.
+// Right-hand sides run one after the other on the same coefficients; in single
+// precision the next one's r and q are in flight while one is swept.  In
+// double precision those 32 registers spill (four waves per SIMD, so that two
+// blocks share a CU: one loads while the other sweeps): three right-hand
+// sides on 256 x 320 x 640 cells 164 ms a solve with them, 122 ms without.
+// 256 x 320 x 640 cells, one right-hand side: 670 us in double precision (5.6
+// TB/s at 72 B per cell) and 360 us in single (40 B), against 1340 and 735 us
+// for one wave per block that walked the 64 rows alone, re-read the
+// coefficients and y, and moved x (144 and 76 B); 61 x 93 x 187 cells 32
+// against 76 us.  Streamed inputs are loaded non-temporally: 128 x 192 x 384
+// cells 8.77 against 9.46 ms a solve without the hint.
+template <typename T, int NR>
+struct Pc2Args {
+    const T *cr, *ct, *cp;  // scaled couplings to the +r, +theta, +phi neighbours
+    const double *w;
+    const T *d;             // modified diagonal
+    T *r[NR], *z[NR];
+    const T *q[NR];
+    double *partials;
+    const Ctl *ctl;         // [NR]
+    Dims dm;
+    int nbi, nbj, nbk;      // blocks per direction
+    int update;             // 1: r -= alpha q first
 };
 
-// PF: rows of loads in flight ahead of the row being scanned.
-template <typename T, int PF>
-__global__ __launch_bounds__(kWave) void k_pc2_solve(Pc2Args<T> a) {
-    static_assert(PF == 1 || PF == 2, "prefetch depth");
-    if (a.ctl->flag != FLAG_RUN) return;
-    const Dims &dm = a.dm;
-    const int blk = blockIdx.x;
-    const int bk = blk % a.nbk, bj = (blk / a.nbk) % a.nbj, bi = blk / (a.nbk * a.nbj);
-    const int lane = threadIdx.x;
-    const int k0 = bk * kPc2K;
-    const int kn = min(kPc2K, dm.np - k0);
-    const bool act = lane < kn;
-    const int k = k0 + (act ? lane : 0);
-    const int ni = min(kPc2I, dm.nr - bi * kPc2I), nj = min(kPc2J, dm.nt - bj * kPc2J);
-    const bool upd = a.update != 0;
-    const T alpha = upd ? (T)a.ctl->alpha : T(0);
-    // distinct arrays: lets the compiler issue later rows' loads ahead of
-    // earlier rows' stores
-    const T *__restrict__ cr = a.cr, *__restrict__ ct = a.ct, *__restrict__ cp = a.cp;
-    const double *__restrict__ w = a.w;
-    const T *__restrict__ dd = a.d, *__restrict__ q = a.q;
-    const T *__restrict__ pp = a.p;
-    T *__restrict__ r = a.r, *__restrict__ x = a.x, *__restrict__ z = a.z;
-    auto cell = [&](int ii, int jj, int kk) -> int64_t {
-        return ((int64_t)(bi * kPc2I + ii) * dm.nt + (bj * kPc2J + jj)) * dm.np + kk;
-    };
-    auto load_f = [&](int ii, int jj) {
-        Pc2Fwd<T> v{0, 0, 0, 0, 0.0, 1, 0, 0, 0};
-        if (act && ii < ni && jj < nj) {
-            const int64_t c = cell(ii, jj, k);
-            v.r = r[c];
-            if (upd) {
-                v.q = q[c];
-                v.x = x[c];
-                v.p = pp[c];
-            }
-            v.w = w[c];
-            v.d = dd[c];
-            if (ii > 0) v.cr = cr[c - dm.plane];
-            if (jj > 0) v.ct = ct[c - dm.np];
-            if (lane > 0) v.cp = cp[c - 1];
-        }
-        return v;
-    };
-    double rw = 0.0, rz = 0.0;
-    T yp[kPc2J];  // previous r plane of the block, one value per theta row
-    // forward sweep: y into z
-#pragma unroll
-    for (int jj = 0; jj < kPc2J; ++jj) yp[jj] = T(0);
-    // rows in order t = ii nj + jj; row t + PF is loaded before row t is scanned
-    auto load_ft = [&](int t) { return load_f(t / nj, t % nj); };
-    Pc2Fwd<T> cur = load_f(0, 0);
-    Pc2Fwd<T> ahead{};
-    if constexpr (PF == 2) ahead = load_ft(1);
-    for (int ii = 0; ii < ni; ++ii) {
-        T yrow = T(0);  // previous theta row
-#pragma unroll
-        for (int jj = 0; jj < kPc2J; ++jj) {
-            if (jj < nj) {
-                const Pc2Fwd<T> nxt = load_ft(ii * nj + jj + PF);
-                T Bc = T(0), Cc = T(0);
-                T rc = cur.r;
-                if (act) {
-                    if (upd) rc -= alpha * cur.q;
-                    const double t = cur.w * (double)rc;
-                    rw += t * t;
-                    T sc = rc;
-                    if (ii > 0) sc += cur.cr * yp[jj];
-                    if (jj > 0) sc += cur.ct * yrow;
-                    const T dinv = T(1) / cur.d;
-                    Bc = sc * dinv;
-                    Cc = cur.cp * dinv;
-                }
-                const T y = affine_scan(Cc, Bc);
-                if (act) {
-                    // (r, M^-1 r) = y^T D y (see below)
-                    rz += (double)cur.d * (double)y * (double)y;
-                    const int64_t c = cell(ii, jj, k);
-                    if (upd) {
-                        r[c] = rc;
-                        x[c] = cur.x + alpha * cur.p;
-                    }
-                    z[c] = y;
-                }
-                yp[jj] = y;
-                yrow = y;
-                if constexpr (PF == 2) {
-                    cur = ahead;
-                    ahead = nxt;
-                } else {
-                    cur = nxt;
-                }
-            }
-        }
-    }
-    // backward sweep: z in place; lane l takes phi offset kn-1-l, so the
-    // recurrence z_k = c_k z_{k+1} + b_k runs up the lanes again
-    const int kb = k0 + (act ? kn - 1 - lane : 0);
-    auto load_b = [&](int ii, int jj) {
-        Pc2Bwd<T> v{0, 0, 1, 0, 0};
-        if (act && ii >= 0 && jj >= 0) {
-            const int64_t c = cell(ii, jj, kb);
-            if (ii < ni - 1) v.cr = cr[c];
-            if (jj < nj - 1) v.ct = ct[c];
-            v.d = dd[c];
-            v.y = z[c];
-            if (lane > 0) v.cp = cp[c];
-        }
-        return v;
-    };
-#pragma unroll
-    for (int jj = 0; jj < kPc2J; ++jj) yp[jj] = T(0);
-    // rows in reverse order; row t - PF is loaded before row t is scanned
-    // (t < 0 divides to ii = 0, jj < 0 or to ii < 0: no load)
-    auto load_bt = [&](int t) { return load_b(t / nj, t % nj); };
-    Pc2Bwd<T> bcur = load_b(ni - 1, nj - 1);
-    Pc2Bwd<T> bahead{};
-    if constexpr (PF == 2) bahead = load_bt(ni * nj - 2);
-    for (int ii = ni - 1; ii >= 0; --ii) {
-        T zrow = T(0);  // next theta row
-#pragma unroll
-        for (int jj = kPc2J - 1; jj >= 0; --jj) {
-            if (jj < nj) {
-                const Pc2Bwd<T> nxt = load_bt(ii * nj + jj - PF);
-                T Bc = T(0), Cc = T(0);
-                if (act) {
-                    T sc = T(0);
-                    if (ii < ni - 1) sc += bcur.cr * yp[jj];
-                    if (jj < nj - 1) sc += bcur.ct * zrow;
-                    const T dinv = T(1) / bcur.d;
-                    Bc = bcur.y + sc * dinv;
-                    Cc = bcur.cp * dinv;
-                }
-                const T zc = affine_scan(Cc, Bc);
-                if (act) z[cell(ii, jj, kb)] = zc;
-                yp[jj] = zc;
-                zrow = zc;
-                if constexpr (PF == 2) {
-                    bcur = bahead;
-                    bahead = nxt;
-                } else {
-                    bcur = nxt;
-                }
-            }
-        }
-    }
-    __shared__ double lds[2];
-    double v2[2] = {rz, rw};
-    block_sum_store<2>(v2, a.partials + (int64_t)blockIdx.x * 2, lds);
+constexpr int kPc2Threads = kWave * kPc2I;
+
+// lane l's value from lane 63 - l
+__device__ inline float lane_reverse(float v, int addr) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(addr, __builtin_bit_cast(int, v)));
+}
+__device__ inline double lane_reverse(double v, int addr) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)b);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)(b >> 32));
+    return __builtin_bit_cast(double, lo | (hi << 32));
 }
 
-// Several right-hand sides under one operator: the block solve of each, as
-// k_pc2_solve, with the couplings, w and the modified diagonal loaded once
-// per cell for all of them (T: double, or float inside double-precision
-// refinement; w and the partial sums are double).  Right-hand side h's
-// partial sums go to partials + 2 h gridDim.x; one whose control block is
-// stopped moves no bytes.
 template <typename T, int NR>
-struct Pc2MultiArgs {
-    const T *cr, *ct, *cp;
-    const double *w;
-    const T *d;
-    T *r[NR], *x[NR], *z[NR];
-    const T *q[NR], *p[NR];
-    double *partials;
-    const Ctl *ctl;  // [NR]
-    Dims dm;
-    int nbi, nbj, nbk;
-    int update;
-};
-
-template <typename T, int NR>
-struct Pc2MFwd {
-    double w;
-    T d, cr, ct, cp;
-    T r[NR], q[NR], x[NR], p[NR];
-};
-template <typename T, int NR>
-struct Pc2MBwd {
-    T cr, ct, d, cp;
-    T y[NR];
-};
-
-template <typename T, int NR>
-__global__ __launch_bounds__(kWave) void k_pc2_solve_multi(Pc2MultiArgs<T, NR> a) {
+__global__ __launch_bounds__(kPc2Threads) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void k_pc2_solve(Pc2Args<T, NR> a) {
+    __shared__ T sCr[kPc2I][kPc2J][kPc2K];  // couplings to the +r neighbour
+    __shared__ T sY[2][kPc2I][kPc2K];       // the row each plane finished last, by step parity
+    __shared__ double sRed[kPc2I][2];
+    // whether the next right-hand side's r and q are loaded ahead (see above)
+    constexpr bool PF = sizeof(T) == 4;
     bool run[NR];
-    T alpha[NR];
     bool any = false;
 #pragma unroll
     for (int h = 0; h < NR; ++h) {
         run[h] = a.ctl[h].flag == FLAG_RUN;
         any = any || run[h];
-        alpha[h] = (a.update != 0 && run[h]) ? (T)a.ctl[h].alpha : T(0);
     }
     if (!any) return;
     const Dims &dm = a.dm;
-    const int blk = blockIdx.x;
+    const int nblk = gridDim.x;
+    const int blk = xcd_remap(blockIdx.x, nblk);
     const int bk = blk % a.nbk, bj = (blk / a.nbk) % a.nbj, bi = blk / (a.nbk * a.nbj);
-    const int lane = threadIdx.x;
-    const int k0 = bk * kPc2K;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int ii = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int I0 = bi * kPc2I, J0 = bj * kPc2J, k0 = bk * kPc2K;
     const int kn = min(kPc2K, dm.np - k0);
+    const int ni = min(kPc2I, dm.nr - I0), nj = min(kPc2J, dm.nt - J0);
     const bool act = lane < kn;
-    const int k = k0 + (act ? lane : 0);
-    const int ni = min(kPc2I, dm.nr - bi * kPc2I), nj = min(kPc2J, dm.nt - bj * kPc2J);
+    const bool in = ii < ni;
+    const int64_t first = (int64_t)min(I0 + ii, dm.nr - 1) * dm.plane;
+    // one r plane of an array (fewer than 2^31 / 7 bytes: the grid check), or nothing
+    auto plane_rsrc = [&](const auto *p, bool on) {
+        return make_rsrc(p ? p + first : p, (p && on && in) ? (uint32_t)(dm.plane * (int64_t)sizeof(*p)) : 0u);
+    };
+    // this lane's cell of row jj; rows and lanes past the grid: out of range
+    auto cell = [&](int jj) { return (uint32_t)((J0 + jj) * dm.np + k0 + lane); };
+    auto off = [&](int jj, bool on, uint32_t es) { return (on && jj < nj) ? cell(jj) * es : kOOB; };
+    constexpr uint32_t ES = sizeof(T);
     const bool upd = a.update != 0;
-    auto cell = [&](int ii, int jj, int kk) -> int64_t {
-        return ((int64_t)(bi * kPc2I + ii) * dm.nt + (bj * kPc2J + jj)) * dm.np + kk;
-    };
-    auto load_f = [&](int ii, int jj) {
-        Pc2MFwd<T, NR> v;
-        v.w = 0.0;
-        v.cr = v.ct = v.cp = T(0);
-        v.d = T(1);
-#pragma unroll
-        for (int h = 0; h < NR; ++h) v.r[h] = v.q[h] = v.x[h] = v.p[h] = T(0);
-        if (act && ii < ni && jj < nj) {
-            const int64_t c = cell(ii, jj, k);
-            v.w = a.w[c];
-            v.d = a.d[c];
-            if (ii > 0) v.cr = a.cr[c - dm.plane];
-            if (jj > 0) v.ct = a.ct[c - dm.np];
-            if (lane > 0) v.cp = a.cp[c - 1];
-#pragma unroll
-            for (int h = 0; h < NR; ++h) {
-                if (run[h]) {
-                    v.r[h] = a.r[h][c];
-                    if (upd) {
-                        v.q[h] = a.q[h][c];
-                        v.x[h] = a.x[h][c];
-                        v.p[h] = a.p[h][c];
-                    }
-                }
-            }
-        }
-        return v;
-    };
-    double rw[NR], rz[NR];
-    T yp[NR][kPc2J];  // previous r plane of the block, per theta row
-#pragma unroll
-    for (int h = 0; h < NR; ++h) {
-        rw[h] = rz[h] = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < kPc2J; ++jj) yp[h][jj] = T(0);
-    }
-    // forward sweep: y into z; row t + 1 is loaded before row t is scanned
-    auto load_ft = [&](int t) { return load_f(t / nj, t % nj); };
-    Pc2MFwd<T, NR> cur = load_f(0, 0);
-    for (int ii = 0; ii < ni; ++ii) {
-        T yrow[NR];
-#pragma unroll
-        for (int h = 0; h < NR; ++h) yrow[h] = T(0);
+
+    T rc[kPc2J], qv[kPc2J];
+    auto load_rq = [&](int h) {
+        const auto Rr = plane_rsrc(a.r[h], run[h]), Rq = plane_rsrc(a.q[h], run[h] && upd);
 #pragma unroll
         for (int jj = 0; jj < kPc2J; ++jj) {
-            if (jj < nj) {
-                const Pc2MFwd<T, NR> nxt = load_ft(ii * nj + jj + 1);
-                const T dinv = T(1) / cur.d;
-                const int64_t c = cell(ii, jj, k);
-#pragma unroll
-                for (int h = 0; h < NR; ++h) {
-                    if (!run[h]) continue;  // uniform across the wave
-                    T Bc = T(0), Cc = T(0);
-                    T rc = cur.r[h];
-                    if (act) {
-                        if (upd) rc -= alpha[h] * cur.q[h];
-                        const double t = cur.w * (double)rc;
-                        rw[h] += t * t;
-                        T sc = rc;
-                        if (ii > 0) sc += cur.cr * yp[h][jj];
-                        if (jj > 0) sc += cur.ct * yrow[h];
-                        Bc = sc * dinv;
-                        Cc = cur.cp * dinv;
-                    }
-                    const T y = affine_scan(Cc, Bc);
-                    if (act) {
-                        rz[h] += (double)cur.d * (double)y * (double)y;  // (r, M^-1 r) = y^T D y
-                        if (upd) {
-                            a.r[h][c] = rc;
-                            a.x[h][c] = cur.x[h] + alpha[h] * cur.p[h];
-                        }
-                        a.z[h][c] = y;
-                    }
-                    yp[h][jj] = y;
-                    yrow[h] = y;
-                }
-                cur = nxt;
-            }
+            rc[jj] = bld<T, 1, kAuxNT>(Rr, off(jj, act, ES)).v[0];
+            qv[jj] = bld<T, 1, kAuxNT>(Rq, off(jj, act, ES)).v[0];
         }
-    }
-    // backward sweep: z in place, lanes reversed (see k_pc2_solve)
-    const int kb = k0 + (act ? kn - 1 - lane : 0);
-    auto load_b = [&](int ii, int jj) {
-        Pc2MBwd<T, NR> v;
-        v.cr = v.ct = v.cp = T(0);
-        v.d = T(1);
-#pragma unroll
-        for (int h = 0; h < NR; ++h) v.y[h] = T(0);
-        if (act && ii >= 0 && jj >= 0) {
-            const int64_t c = cell(ii, jj, kb);
-            if (ii < ni - 1) v.cr = a.cr[c];
-            if (jj < nj - 1) v.ct = a.ct[c];
-            v.d = a.d[c];
-            if (lane > 0) v.cp = a.cp[c];
-#pragma unroll
-            for (int h = 0; h < NR; ++h)
-                if (run[h]) v.y[h] = a.z[h][c];
-        }
-        return v;
     };
-    auto load_bt = [&](int t) { return load_b(t / nj, t % nj); };
+    T crv[kPc2J], d[kPc2J], dinv[kPc2J], ctm[kPc2J], cp[kPc2J];
+    double w[kPc2J];
+    {
+        const auto Rcr = plane_rsrc(a.cr, ii < ni - 1), Rct = plane_rsrc(a.ct, true), Rcp = plane_rsrc(a.cp, true),
+                   Rd = plane_rsrc(a.d, true), Rw = plane_rsrc(a.w, true);
 #pragma unroll
-    for (int h = 0; h < NR; ++h)
+        for (int jj = 0; jj < kPc2J; ++jj) crv[jj] = bld<T, 1, kAuxNT>(Rcr, off(jj, act, ES)).v[0];
+        load_rq(0);
 #pragma unroll
-        for (int jj = 0; jj < kPc2J; ++jj) yp[h][jj] = T(0);
-    Pc2MBwd<T, NR> bcur = load_b(ni - 1, nj - 1);
-    for (int ii = ni - 1; ii >= 0; --ii) {
-        T zrow[NR];
-#pragma unroll
-        for (int h = 0; h < NR; ++h) zrow[h] = T(0);
-#pragma unroll
-        for (int jj = kPc2J - 1; jj >= 0; --jj) {
-            if (jj < nj) {
-                const Pc2MBwd<T, NR> nxt = load_bt(ii * nj + jj - 1);
-                const T dinv = T(1) / bcur.d;
-#pragma unroll
-                for (int h = 0; h < NR; ++h) {
-                    if (!run[h]) continue;
-                    T Bc = T(0), Cc = T(0);
-                    if (act) {
-                        T sc = T(0);
-                        if (ii < ni - 1) sc += bcur.cr * yp[h][jj];
-                        if (jj < nj - 1) sc += bcur.ct * zrow[h];
-                        Bc = bcur.y[h] + sc * dinv;
-                        Cc = bcur.cp * dinv;
-                    }
-                    const T zc = affine_scan(Cc, Bc);
-                    if (act) a.z[h][cell(ii, jj, kb)] = zc;
-                    yp[h][jj] = zc;
-                    zrow[h] = zc;
-                }
-                bcur = nxt;
-            }
+        for (int jj = 0; jj < kPc2J; ++jj) {
+            d[jj] = bld<T, 1, kAuxNT>(Rd, off(jj, act, ES)).v[0];
+            cp[jj] = bld<T, 1, kAuxNT>(Rcp, off(jj, lane < kn - 1, ES)).v[0];
+            ctm[jj] = (jj > 0) ? bld<T, 1, kAuxNT>(Rct, off(jj, act, ES) - (uint32_t)dm.np * ES).v[0] : T(0);
         }
+#pragma unroll
+        for (int jj = 0; jj < kPc2J; ++jj) w[jj] = bld<double, 1, kAuxNT>(Rw, off(jj, act, 8u)).v[0];
     }
-    __shared__ double lds[2];
+#pragma unroll
+    for (int jj = 0; jj < kPc2J; ++jj) sCr[ii][jj][lane] = crv[jj];
+#pragma unroll
+    for (int jj = 0; jj < kPc2J; ++jj) {
+        if (!(in && act && jj < nj)) d[jj] = T(1);
+        dinv[jj] = T(1) / d[jj];
+    }
+    const int rlane = kWave - 1 - lane, raddr = 4 * rlane;
+
 #pragma unroll
     for (int h = 0; h < NR; ++h) {
-        if (!run[h]) continue;  // uniform across the block
-        double v2[2] = {rz[h], rw[h]};
-        block_sum_store<2>(v2, a.partials + (int64_t)(2 * h) * gridDim.x + (int64_t)blockIdx.x * 2, lds);
+        if (!run[h]) {  // uniform across the block
+            if (PF && h + 1 < NR) load_rq(h + 1);
+            continue;
+        }
+        if (!PF && h > 0) load_rq(h);
+        const T alpha = upd ? (T)a.ctl[h].alpha : T(0);
+        double rz = 0.0, rw = 0.0;
+        T y[kPc2J];
+        {
+            const auto Rr = plane_rsrc(a.r[h], upd);
+#pragma unroll
+            for (int jj = 0; jj < kPc2J; ++jj) {
+                const T v = rc[jj] - alpha * qv[jj];
+                y[jj] = v;
+                bst<T, 1, kAuxNT>(Rr, off(jj, act, ES), VecT<T, 1>{{v}});
+                const double t = w[jj] * (double)v;
+                rw = __builtin_fma(t, t, rw);
+            }
+        }
+        if (PF && h + 1 < NR) load_rq(h + 1);
+        // ---- forward sweep
+        for (int t = 0; t < min(ii, ni + nj - 1); ++t) __syncthreads();
+        if (in) {
+#pragma unroll
+            for (int jj = 0; jj < kPc2J; ++jj) {
+                if (jj < nj) {
+                    T sc = y[jj];
+                    if (ii > 0) sc = fma(sCr[ii - 1][jj][lane], sY[(ii + jj - 1) & 1][ii - 1][lane], sc);
+                    if (jj > 0) sc = fma(ctm[jj], y[jj > 0 ? jj - 1 : 0], sc);
+                    // the first lane has no -phi neighbour: lane_prev gives it 0
+                    const T v = affine_scan(lane_prev(cp[jj]) * dinv[jj], sc * dinv[jj]);
+                    y[jj] = v;
+                    sY[(ii + jj) & 1][ii][lane] = v;
+                    __syncthreads();
+                    rz = __builtin_fma((double)d[jj] * (double)v, (double)v, rz);
+                }
+            }
+            for (int t = 0; t < ni - 1 - ii; ++t) __syncthreads();
+        } else {
+            for (int t = 0; t < ni + nj - 1 - min(ii, ni + nj - 1); ++t) __syncthreads();
+        }
+        // ---- backward sweep, lanes reversed
+        const auto Rz = plane_rsrc(a.z[h], true);
+        const uint32_t zoff = (rlane < kn) ? (uint32_t)(J0 * dm.np + k0 + rlane) * ES : kOOB;
+        if (in) {
+            for (int t = 0; t < ni - 1 - ii; ++t) __syncthreads();
+            T zrow = T(0);
+#pragma unroll
+            for (int jj = kPc2J - 1; jj >= 0; --jj) {
+                if (jj < nj) {
+                    const int step = (ni - 1 - ii) + (nj - 1 - jj);
+                    T sc = T(0);
+                    if (ii < ni - 1) sc = sCr[ii][jj][rlane] * sY[(step + 1) & 1][ii + 1 < kPc2I ? ii + 1 : ii][lane];
+                    if (jj < kPc2J - 1) sc = fma(lane_reverse(ctm[jj < kPc2J - 1 ? jj + 1 : jj], raddr), zrow, sc);
+                    const T di = lane_reverse(dinv[jj], raddr);
+                    zrow = affine_scan(lane_reverse(cp[jj], raddr) * di, fma(sc, di, lane_reverse(y[jj], raddr)));
+                    sY[step & 1][ii][lane] = zrow;
+                    __syncthreads();
+                    bst<T, 1>(Rz, (zoff == kOOB) ? kOOB : zoff + (uint32_t)(jj * dm.np) * ES, VecT<T, 1>{{zrow}});
+                }
+            }
+            for (int t = 0; t < ii; ++t) __syncthreads();
+        } else {
+            for (int t = 0; t < ni + nj - 1; ++t) __syncthreads();
+        }
+        // ---- the block's sums
+        rz = wave_sum(rz);
+        rw = wave_sum(rw);
+        if (lane == 0) {
+            sRed[ii][0] = rz;
+            sRed[ii][1] = rw;
+        }
         __syncthreads();
+        if (threadIdx.x < 2) {
+            double v = 0.0;
+            for (int u = 0; u < ni; ++u) v += sRed[u][threadIdx.x];
+            a.partials[(int64_t)2 * h * nblk + 2 * (int64_t)blk + threadIdx.x] = v;
+        }
+        if (h + 1 < NR) __syncthreads();
     }
 }
 
@@ -642,12 +477,13 @@ __global__ __launch_bounds__(kRedThreads) void k_pc2_fin_a(const double *partial
     if (threadIdx.x != 0) return;
     const double PQ = sh[0];
     ctl->pq = PQ;
+    ctl->launches += 1;
     if (!(PQ > 0.0) || !isfinite(PQ)) {
         ctl->flag = FLAG_BREAK;
         ctl->conv_iter = ctl->iter;
-        ctl->alpha = 0.0;
         return;
     }
+    ctl->alpha_prev = ctl->alpha;
     ctl->alpha = ctl->rr / PQ;
 }
 
@@ -695,6 +531,33 @@ __global__ __launch_bounds__(kRedThreads) void k_pc2_fin_b(const double *partial
     }
     ctl->beta = is_first ? 0.0 : RZ / ctl->rr;
     ctl->rr = RZ;
+}
+
+// After a PC2 run: x moves in every second direction launch only, two updates
+// at a time (IterArgs::xstep: launches 2, 4, ... of a run, each bringing x up
+// to the direction before its own), so T finished iterations leave one or two
+// updates (none after a breakdown found by such a launch), made here in the
+// same order with the same fused multiply-adds.  p of iteration t (0-based)
+// is in p[(iter0 + t + 1) & 1]; alpha is the last iteration's, alpha_prev the
+// one's before.  blockIdx.y is the right-hand side.
+template <typename T>
+__global__ __launch_bounds__(256) void k_pc2_catchup(CatchupArgs<T> a) {
+    const int c = blockIdx.y;
+    const Ctl *ctl = a.ctl + c;
+    const int ran = ctl->launches;  // direction launches that did work
+    const int last = (ctl->flag == FLAG_RUN) ? ctl->iter : ctl->conv_iter;
+    const int T_ = last - a.iter0;             // finished iterations
+    const int done = ((ran - 1) / 2) * 2;      // updates made by the launches
+    T *x = a.x[c];
+    if (ran < 1 || T_ <= done || !x) return;
+    const bool two = T_ - done == 2;
+    const T a1 = (T)ctl->alpha, a0 = (T)ctl->alpha_prev;
+    const T *p1 = a.p[c][(a.iter0 + T_) & 1], *p0 = a.p[c][(a.iter0 + T_ + 1) & 1];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * 256) {
+        T v = x[i];
+        if (two) v = v + a0 * p0[i];
+        x[i] = v + a1 * p1[i];
+    }
 }
 
 }  // namespace mas

@@ -209,3 +209,25 @@ def test_pc2_error_paths():
         op64.solve_multi(B, S.make_opts(precond="pc2", precision="fp32_refined"))
     x, info = op64.solve(rhs, S.make_opts(max_iters=2, max_restarts=0, precond="pc2"))
     assert info["status"] == abi.MAS_ENOTCONV and info["iters"] == 2
+
+
+@pytest.mark.parametrize("iters", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("shape", [(9, 17, 33), (8, 8, 64), (17, 9, 130)])
+def test_pc2_stopped_after_any_iteration(shape, iters):
+    """x moves two iterations at a time; a run stopped after an odd or an even
+    count, alone or beside another right-hand side, holds the oracle's x_k
+    (same bound per iteration as the iterate test)."""
+    import torch
+
+    p = problem(shape, (0, 1))
+    _, op = gpu_operator(p)
+    ora = oracle_operator(p)
+    b = ora.rhs_to_b(p.rhs)
+    opts = S.make_opts(rtol=0.0, precond="pc2", max_iters=iters, max_restarts=0)
+    rhs = to_dev(p.rhs)
+    with pytest.warns(UserWarning, match="did not converge"):
+        x, _ = op.solve(rhs, opts)
+        both, _ = op.solve_multi(torch.stack([rhs, 2.0 * rhs]), opts)
+    want = ora.pcg_pc2(b, BLOCKS, tol=0.0, max_iters=iters)[0]
+    assert rel(to_host(x), want) <= 1e-11 * iters
+    assert torch.equal(both[0], x) and torch.equal(both[1], 2.0 * x)
