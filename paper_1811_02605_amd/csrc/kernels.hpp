@@ -108,8 +108,19 @@ __device__ inline double wave_sum(double v) {
     return v;
 }
 
-// Sum NV values over the block in a fixed order; thread 0 writes them to out.
-template <int NV>
+// Data that blocks of one launch pass to each other: stores and loads at agent
+// scope go past the L2 of the XCD (which is not coherent with the other seven)
+// with no write-back or invalidation of anything else.
+__device__ inline void st_agent(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline double ld_agent(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum NV values over the block in a fixed order; the first NV threads write
+// them to out (AGENT: at agent scope, for another block of this launch).
+template <int NV, bool AGENT = false>
 __device__ inline void block_sum_store(double (&v)[NV], double *out, double *lds) {
     const int tid = threadIdx.x + threadIdx.y * blockDim.x;
     const int lane = tid & (kWave - 1);
@@ -122,41 +133,79 @@ __device__ inline void block_sum_store(double (&v)[NV], double *out, double *lds
         for (int t = 0; t < NV; ++t) lds[wv * NV + t] = v[t];
     }
     __syncthreads();
-    if (threadIdx.x == 0 && threadIdx.y == 0) {
-        for (int t = 0; t < NV; ++t) {
-            double s = 0.0;
-            for (int u = 0; u < nw; ++u) s += lds[u * NV + t];
-            out[t] = s;
-        }
+    static_assert(NV <= kWave, "one wave writes the sums");
+    if (tid < NV) {
+        double s = 0.0;
+        for (int u = 0; u < nw; ++u) s += lds[u * NV + tid];
+        if constexpr (AGENT) st_agent(out + tid, s);
+        else out[tid] = s;
     }
 }
 
+// Whether this block is the last of nblk to come here, uniform across the
+// block.  What the block's first wave has stored at agent scope before is then
+// visible, for the last block, to agent-scope loads: the wave waits until its
+// stores have been acknowledged before it counts itself (relaxed: a release
+// would write back the whole L2, which cost the iteration kernel 17% on the
+// 52.4M-cell grid).  *count is zero before the launch and after it.
+__device__ inline bool last_block(uint32_t *count, uint32_t nblk) {
+    __shared__ int last;
+    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+    if (tid < kWave) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (tid == 0) {
+            const uint32_t n = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = n == nblk - 1;
+            if (n == nblk - 1) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    return last != 0;
+}
+
 // ---------------------------------------------------------------- CG finalize
-// Fixed-order sum of the kNV partials of right-hand side c over nblk blocks
-// ([nblk][nrhs][kNV]) by the NT threads of one block: thread t adds blocks
-// t, t + NT, ... in order, the waves combine by a butterfly, the wave sums
-// are added in wave order (bitwise reproducible).  Every thread gets the
-// sums.
-template <int NT>
-__device__ inline void sum_partials(const double *partials, int nblk, int nrhs, int c,
-                                    double (&out)[kNV], double *lds) {
-    double v[kNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblk; b += NT) {
+// Fixed-order sum of NV partials per block ([nblk][stride], partials pointing
+// at the first of them) over nblk blocks by the NT threads of one block, read
+// at agent scope: thread t adds blocks t, t + NT, ... in order, the waves
+// combine by a butterfly, the wave sums are added in wave order (bitwise
+// reproducible).  Every thread gets the sums.  kSumAhead blocks' partials are
+// loaded before they are added: the loads miss every cache on the way (one at
+// a time, the persistent run on 32 x 32 x 64 cells took 12.8 instead of 10.6 us
+// per iteration).
+constexpr int kSumAhead = 4;
+template <int NT, int NV>
+__device__ inline void sum_partials(const double *partials, int nblk, int stride, double (&out)[NV],
+                                    double *lds) {
+    double v[NV];
 #pragma unroll
-        for (int t = 0; t < kNV; ++t) v[t] += partials[((int64_t)b * nrhs + c) * kNV + t];
+    for (int t = 0; t < NV; ++t) v[t] = 0.0;
+    for (int b0 = threadIdx.x; b0 < nblk; b0 += NT * kSumAhead) {
+        double w[kSumAhead][NV];
+#pragma unroll
+        for (int u = 0; u < kSumAhead; ++u) {
+            const int b = min(b0 + u * NT, nblk - 1);
+#pragma unroll
+            for (int t = 0; t < NV; ++t) w[u][t] = ld_agent(partials + (int64_t)b * stride + t);
+        }
+#pragma unroll
+        for (int u = 0; u < kSumAhead; ++u)
+            if (b0 + u * NT < nblk) {
+#pragma unroll
+                for (int t = 0; t < NV; ++t) v[t] += w[u][t];
+            }
     }
 #pragma unroll
-    for (int t = 0; t < kNV; ++t) v[t] = wave_sum(v[t]);
+    for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
     const int wv = threadIdx.x / kWave;
     if ((threadIdx.x & (kWave - 1)) == 0) {
 #pragma unroll
-        for (int t = 0; t < kNV; ++t) lds[wv * kNV + t] = v[t];
+        for (int t = 0; t < NV; ++t) lds[wv * NV + t] = v[t];
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < kNV; ++t) {
+    for (int t = 0; t < NV; ++t) {
         double s = 0.0;
-        for (int u = 0; u < NT / kWave; ++u) s += lds[u * kNV + t];
+        for (int u = 0; u < NT / kWave; ++u) s += lds[u * NV + t];
         out[t] = s;
     }
     __syncthreads();
@@ -253,7 +302,9 @@ struct IterArgs {
     const T *cr, *ct, *cp;
     const double *w;
     double *partials;  // [nblk][NR][kNV]
-    const Ctl *ctl;    // [NR]
+    Ctl *ctl;          // [NR]
+    uint32_t *count;   // blocks that have finished (last_block)
+    int alpha_only;    // 1: a PC2 direction launch, whose finalize only sets alpha
     Dims d;
     int tiles_i, tiles_k, tiles_j, ti;  // r chunks, phi segments, theta tiles; r planes per chunk
     int nblk;
@@ -940,7 +991,21 @@ __device__ __forceinline__ void pcg_iter_body(const IterArgs<T> &a, const IterSc
         }
     }
     __shared__ double sRed[WPB * NR * kNV];
-    block_sum_store<NR * kNV>(acc, a.partials + (int64_t)L * NR * kNV, sRed);
+    block_sum_store<NR * kNV, true>(acc, a.partials + (int64_t)L * NR * kNV, sRed);
+}
+
+// After the SpMV of a PC2 iteration (one thread): alpha = (r, z) / (p, q), or
+// a breakdown, which leaves the last iteration's alphas for x.
+__device__ inline void pc2_alpha(Ctl *ctl, double PQ) {
+    ctl->pq = PQ;
+    ctl->launches += 1;
+    if (!(PQ > 0.0) || !isfinite(PQ)) {
+        ctl->flag = FLAG_BREAK;
+        ctl->conv_iter = ctl->iter;
+        return;
+    }
+    ctl->alpha_prev = ctl->alpha;
+    ctl->alpha = ctl->rr / PQ;
 }
 
 template <typename T, int NR, int WPB, int RPW, int V, bool HALO>
@@ -952,23 +1017,27 @@ void k_pcg_iter(IterArgs<T> a) {
     IterScalars<T, NR> sc;
     if (!iter_scalars<T, NR>(a.ctl, sc)) return;
     pcg_iter_body<T, NR, WPB, RPW, V, HALO>(a, sc);
-}
-
-// One block: the finalize of right-hand side blockIdx.x after an iteration
-// kernel (partials [nblk][gridDim.x][kNV]).  A launch of its own: folding it
-// into the iteration kernel (the last block to finish sums the partials
-// after an agent-scope fence) made that kernel 17% slower on the 52.4M-cell
-// grid, the fence writing back the XCD's L2, and gained nothing on small
-// grids.
-__global__ __launch_bounds__(kRedThreads) void k_finalize(const double *partials, int nblk,
-                                                         Ctl *ctl_all) {
-    const int c = blockIdx.x, nrhs = gridDim.x;
-    Ctl *ctl = ctl_all + c;
-    if (ctl->flag != FLAG_RUN) return;
-    __shared__ double lds[(kRedThreads / kWave) * kNV];
-    double S[kNV];
-    sum_partials<kRedThreads>(partials, nblk, nrhs, c, S, lds);
-    if (threadIdx.x == 0) pcg_finalize(ctl, S);
+    if (!last_block(a.count, (uint32_t)a.nblk)) return;
+    // The finalize, by the block that finishes last.  A launch of its own took
+    // 4.5 us and a gap per iteration (5 x 3 of them with three PC2 right-hand
+    // sides: 12.9 -> 11.9 ms a solve on 96 x 160 x 320 cells; one PC1 solve on
+    // 64 x 96 x 192 cells 3.89 -> 3.79 ms; nothing lost on 52.4M cells).
+    constexpr int NT = kWave * WPB;
+    __shared__ double lds[WPB * kNV];
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+        if (!sc.run[c]) continue;  // uniform
+        const double *part = a.partials + c * kNV;
+        if (a.alpha_only) {
+            double S[1];
+            sum_partials<NT, 1>(part, a.nblk, NR * kNV, S, lds);
+            if (threadIdx.x == 0) pc2_alpha(a.ctl + c, S[0]);
+        } else {
+            double S[kNV];
+            sum_partials<NT, kNV>(part, a.nblk, NR * kNV, S, lds);
+            if (threadIdx.x == 0) pcg_finalize(a.ctl + c, S);
+        }
+    }
 }
 
 // ---------------------------------------------------------------- persistent PCG run
@@ -977,17 +1046,18 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(const double *partials
 // at once (such a grid spends an iteration on launches and latency, not on
 // bandwidth).  Each pass of the loop is one iteration (pcg_iter_body, edge
 // cells loaded directly), then a grid barrier, then every block sums the
-// partial sums itself, in k_finalize's fixed order, and applies
+// partial sums itself, in the launched form's fixed order, and applies
 // pcg_finalize to its own copies of the control blocks (block 0 also writes
 // them back): every block takes the same decisions, and the results equal
-// those of k_pcg_iter and k_finalize launched per iteration, bit for bit.
+// those of k_pcg_iter launched per iteration, bit for bit.
 // The loop ends when no right-hand side runs any more.  The
 // vectors, partial sums and records are double-buffered by parity as
 // there, and a block starts iteration k + 1 only after every block has
 // finished iteration k, so no block overwrites what another still reads.
 struct PersistSync {
-    uint32_t bar;  // barrier arrivals, zero at launch
-    int32_t err;   // 1: a block gave up waiting at a barrier
+    uint32_t bar;    // barrier arrivals, zero at launch
+    int32_t err;     // 1: a block gave up waiting at a barrier
+    uint32_t count;  // blocks of a launch that have finished (last_block)
 };
 
 template <typename T, int NR>
@@ -995,7 +1065,7 @@ struct PersistArgs {
     IterArgs<T> it;                   // shared fields; buffers and partials set per iteration
     T *r[NR][2], *p[NR][2], *q[NR][2];  // by parity: iteration k reads index k & 1
     double *partials[2];              // by parity, [nblk][NR][kNV] each
-    Ctl *ctl;                         // [NR] (k_ctl_init has set them)
+    Ctl *ctl;                         // [NR] (k_run_init has set them)
     PersistSync *sync;
     int iter0;                        // the run's first iteration index
     int keep_p[NR];                   // the first iteration continues the direction in p[c][iter0 & 1]
@@ -1070,7 +1140,7 @@ __global__ __launch_bounds__(kWave *WPB) void k_pcg_persist(PersistArgs<T, NR> a
         for (int c = 0; c < NR; ++c) {
             if (lc[c].flag != FLAG_RUN) continue;  // uniform: every thread reads the same flag
             double S[kNV];
-            sum_partials<kRedThreads>(it.partials, it.nblk, NR, c, S, lds);
+            sum_partials<kRedThreads, kNV>(it.partials + c * kNV, it.nblk, NR * kNV, S, lds);
             if (threadIdx.x == 0) {
                 pcg_finalize(&lc[c], S);
                 if (blockIdx.x == 0) a.ctl[c] = lc[c];
@@ -1079,13 +1149,6 @@ __global__ __launch_bounds__(kWave *WPB) void k_pcg_persist(PersistArgs<T, NR> a
             any = any || lc[c].flag == FLAG_RUN;
         }
         if (!any) return;
-    }
-}
-
-__global__ void k_persist_init(PersistSync *sync) {
-    if (threadIdx.x == 0) {
-        sync->bar = 0u;
-        sync->err = 0;
     }
 }
 
@@ -1137,29 +1200,38 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(const double *partials, 
     }
 }
 
-// Reset the control block for a new PCG run (a kernel, not a memset, so it
-// is safe inside captured graphs as well).
+// Reset the control blocks and the counters for a new PCG run of n right-hand
+// sides (a kernel, not a memset, so it is safe inside captured graphs as well).
 // flag0 = FLAG_RUN starts the run; another flag leaves this control block
 // (one right-hand side of several) stopped from the start.
 // check0: the first iteration kernel of the run forms ||W r||^2 (in mode 0
 // its ratio to (r, r) starts the prediction of the check); then every
 // check_every-th and those near the threshold (pcg_finalize).
-__global__ void k_ctl_init(Ctl *ctl, int mode, int iter0, int max_iter, double tol2,
-                           double beta0, int flag0, int check0, int check_every) {
-    if (threadIdx.x != 0) return;
+struct RunInit {
+    int n, mode, iter0, check0, check_every;
+    int max_iter[kMaxRhs], flag0[kMaxRhs];
+    double tol2[kMaxRhs], beta0[kMaxRhs];
+};
+
+__global__ void k_run_init(Ctl *ctl_all, PersistSync *sync, RunInit in) {
+    if (threadIdx.x == 0) *sync = PersistSync{0u, 0, 0u};
+    if ((int)threadIdx.x >= in.n) return;
+    const int c = threadIdx.x;
+    Ctl *ctl = ctl_all + c;
     ctl->alpha = 0.0;
-    ctl->beta = beta0;
+    ctl->alpha_prev = 0.0;
+    ctl->beta = in.beta0[c];
     ctl->rr = 0.0;
     ctl->rw = 0.0;
-    ctl->tol2 = tol2;
+    ctl->tol2 = in.tol2[c];
     ctl->wratio = 0.0;
-    ctl->flag = flag0;
-    ctl->iter = iter0;
-    ctl->max_iter = max_iter;
-    ctl->mode = mode;
+    ctl->flag = in.flag0[c];
+    ctl->iter = in.iter0;
+    ctl->max_iter = in.max_iter[c];
+    ctl->mode = in.mode;
     ctl->conv_iter = -1;
-    ctl->check = check0;
-    ctl->check_every = check_every > 0 ? check_every : 1;
+    ctl->check = in.check0;
+    ctl->check_every = in.check_every > 0 ? in.check_every : 1;
     ctl->launches = 0;
 }
 
@@ -1723,10 +1795,10 @@ __global__ __launch_bounds__(kWave *kSimpleJ) void k_unscale(const double *w, Di
 
 // Refinement update x^ += d^ + alpha p (double accumulation of the single-
 // precision correction and of the pending step, alpha read from the control
-// block; alpha = 0 for a restarted inner solve), then d^ = 0.
+// block; 0 with none, for a restarted inner solve), then d^ = 0.
 __global__ __launch_bounds__(kWave *kSimpleJ) void k_refine_fold(float *dh, const float *p,
                                                                  const Ctl *ctl, Dims d, double *x) {
-    const double alpha = ctl->alpha;
+    const double alpha = ctl ? ctl->alpha : 0.0;
     MAS_SIMPLE_LOOP(d, {
         if (cell.ok) {
             x[cell.c] = x[cell.c] + ((double)dh[cell.c] + alpha * (double)p[cell.c]);

@@ -819,6 +819,24 @@ static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
     return 1;
 }
 
+// Control blocks and counters of a PC1 run (one launch for all right-hand sides).
+template <typename T, int NR>
+static void start_run(Ctx &cx, const RhsSet<T> &v, int mode, int iter0, int check_every) {
+    RunInit in{};
+    in.n = NR;
+    in.mode = mode;
+    in.iter0 = iter0;
+    in.check0 = mode == 0 ? 1 : 0;
+    in.check_every = check_every;
+    for (int h = 0; h < NR; ++h) {
+        in.max_iter[h] = v.max_iter[h];
+        in.flag0[h] = v.active[h] ? FLAG_RUN : FLAG_CONV;
+        in.tol2[h] = v.tol2[h];
+        in.beta0[h] = v.keep_p[h] ? v.beta0[h] : 0.0;
+    }
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(kWave), 0, cx.stream, cx.ctl, cx.sync, in);
+}
+
 // A PC1 run of NR right-hand sides in one cooperative launch of
 // k_pcg_persist: the same control-block set-up, iterations, stopping and
 // results as run_pcg's launches per iteration, bit for bit.
@@ -829,14 +847,8 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     const Shape &s = op->s;
     hipStream_t st = cx.stream;
     bool work = false;
-    for (int h = 0; h < NR; ++h) {
-        const double beta0 = v.keep_p[h] ? v.beta0[h] : 0.0;
-        hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, cx.ctl + h, mode, iter0,
-                           v.max_iter[h], v.tol2[h], beta0, v.active[h] ? FLAG_RUN : FLAG_CONV,
-                           mode == 0 ? 1 : 0, check_every);
-        work = work || (v.active[h] && v.max_iter[h] >= iter0);
-    }
-    hipLaunchKernelGGL(k_persist_init, dim3(1), dim3(64), 0, st, cx.sync);
+    for (int h = 0; h < NR; ++h) work = work || (v.active[h] && v.max_iter[h] >= iter0);
+    start_run<T, NR>(cx, v, mode, iter0, check_every);
     LAUNCHCHK();
     cx.launched = MAS_LAUNCH_PERSISTENT;
     if (work) {
@@ -917,13 +929,9 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     const Shape &s = op->s;
     hipStream_t st = cx.stream;
     int max_iter = iter0;
-    for (int h = 0; h < NR; ++h) {
-        const double beta0 = v.keep_p[h] ? v.beta0[h] : 0.0;
-        hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, cx.ctl + h, mode, iter0,
-                           v.max_iter[h], v.tol2[h], beta0, v.active[h] ? FLAG_RUN : FLAG_CONV,
-                           mode == 0 ? 1 : 0, check_every);
+    for (int h = 0; h < NR; ++h)
         if (v.active[h]) max_iter = std::max(max_iter, v.max_iter[h]);
-    }
+    start_run<T, NR>(cx, v, mode, iter0, check_every);
     LAUNCHCHK();
     FlagPoll poll(cx);
     int e = poll.init();
@@ -936,6 +944,7 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     a.w = op->w;
     a.partials = cx.partials;
     a.ctl = cx.ctl;
+    a.count = &cx.sync->count;
     a.d = s.dims();
     const int V = iter_vec<T>(s.np, NR);
     a.tiles_i = s.tiles_i(V, cx.chunk);
@@ -1003,8 +1012,6 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
             else
                 halo ? go(I1{}, Tr{}) : go(I1{}, F{});
             if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
-            hipLaunchKernelGGL(k_finalize, dim3(NR), dim3(kRedThreads), 0, st, cx.partials, a.nblk,
-                               cx.ctl);
         }
         LAUNCHCHK();
         e = poll.after_batch(NR, &stop);
@@ -1087,12 +1094,16 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     int nbi, nbj, nbk;
     const int64_t nb = pc2_blocks(s, &nbi, &nbj, &nbk);
     int kmax = iter0;
+    RunInit in{};
+    in.n = NR;
+    in.iter0 = iter0;
     for (int h = 0; h < NR; ++h) {
-        hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, cx.ctl + h, 0, iter0,
-                           active[h] ? max_iter[h] : iter0, tol2[h], 0.0,
-                           (int)(active[h] ? FLAG_RUN : FLAG_CONV), 0, 1);
+        in.max_iter[h] = active[h] ? max_iter[h] : iter0;
+        in.flag0[h] = active[h] ? FLAG_RUN : FLAG_CONV;
+        in.tol2[h] = tol2[h];
         if (active[h]) kmax = std::max(kmax, max_iter[h]);
     }
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(kWave), 0, st, cx.ctl, cx.sync, in);
     const T *cc[3];
     if constexpr (std::is_same<T, float>::value) {
         for (int t = 0; t < 3; ++t) cc[t] = op->c32[t];
@@ -1107,6 +1118,7 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     a.d = v.d;
     a.partials = cx.partials;
     a.ctl = cx.ctl;
+    a.count = &cx.sync->count;
     a.dm = s.dims();
     a.nbi = nbi;
     a.nbj = nbj;
@@ -1118,6 +1130,8 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     it.w = op->w;
     it.partials = cx.partials;
     it.ctl = cx.ctl;
+    it.count = &cx.sync->count;
+    it.alpha_only = 1;
     it.d = s.dims();
     const int V = iter_vec<T>(s.np, NR);
     it.tiles_i = s.tiles_i(V, cx.chunk);
@@ -1137,9 +1151,6 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     auto solve_all = [&](int is_first) {
         a.update = is_first ? 0 : 1;
         hipLaunchKernelGGL((k_pc2_solve<T, NR>), dim3((unsigned)nb), dim3(kPc2Threads), 0, st, a);
-        for (int h = 0; h < NR; ++h)
-            hipLaunchKernelGGL(k_pc2_fin_b, dim3(1), dim3(kRedThreads), 0, st,
-                               cx.partials + 2 * h * nb, (int)nb, cx.ctl + h, is_first);
     };
     // z = M^-1 r of the initial residuals, (r, z), the stopping tests
     solve_all(1);
@@ -1176,9 +1187,6 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
             else
                 hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, 1, false>), igrid, iblock,
                                    0, st, it);
-            for (int h = 0; h < NR; ++h)
-                hipLaunchKernelGGL(k_pc2_fin_a, dim3(1), dim3(kRedThreads), 0, st,
-                                   cx.partials + h * kNV, it.nblk, (int)(NR * kNV), cx.ctl + h);
             solve_all(0);
             if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
         }
@@ -1543,10 +1551,8 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
                 k0 = pr.last_iter[0] + 1;
             } else {
                 // classical refinement: x^ += d^; the next inner solve restarts
-                hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, cx.stream, cx.ctl, 1, 0, 0,
-                                   0.0, 0.0, (int)FLAG_RUN, 0, 1);  // alpha = 0 for the fold
-                hipLaunchKernelGGL(k_refine_fold, sgrid, sblock, 0, cx.stream, dh, p[nxt], cx.ctl,
-                                   d, x);
+                hipLaunchKernelGGL(k_refine_fold, sgrid, sblock, 0, cx.stream, dh, p[nxt],
+                                   (const Ctl *)nullptr, d, x);
                 LAUNCHCHK();
                 st = residual<float>(cx, bhat, x, r[0], &rw2, &rr2);
                 if (st != MAS_OK) return st;
@@ -1986,10 +1992,8 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
                 }
             } else {
                 // classical refinement: x^ += d^; the next inner solve restarts
-                hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, stream, cx.ctl + h, 1, 0, 0,
-                                   0.0, 0.0, (int)FLAG_RUN, 0, 1);  // alpha = 0 for the fold
                 hipLaunchKernelGGL(k_refine_fold, sgrid, sblock, 0, stream, dh[h], v.p[h][0],
-                                   cx.ctl + h, d, xh[h]);
+                                   (const Ctl *)nullptr, d, xh[h]);
                 LAUNCHCHK();
                 st = residual<float>(cx, bhat[h], xh[h], v.r[h][0], &rw2[h], &rr2[h]);
                 if (st != MAS_OK) return st;

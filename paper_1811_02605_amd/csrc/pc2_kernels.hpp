@@ -284,13 +284,40 @@ struct Pc2Args {
     T *r[NR], *z[NR];
     const T *q[NR];
     double *partials;
-    const Ctl *ctl;         // [NR]
+    Ctl *ctl;               // [NR]
+    uint32_t *count;        // blocks that have finished (last_block)
     Dims dm;
     int nbi, nbj, nbk;      // blocks per direction
-    int update;             // 1: r -= alpha q first
+    int update;             // 1: r -= alpha q first; 0: the solve of a run's initial residual
 };
 
 constexpr int kPc2Threads = kWave * kPc2I;
+
+// After the block solves (one thread): the stopping test on RW = ||W r||^2 and
+// beta from RZ = (r, z).  ctl->iter counts finished iterations; first marks the
+// solve of the initial residual (no iteration finished yet).
+__device__ inline void pc2_beta(Ctl *ctl, double RZ, double RW, bool first) {
+    const int k = first ? ctl->iter : ctl->iter + 1;
+    ctl->iter = k;
+    ctl->rw = RW;
+    if (RW <= ctl->tol2 || RW == 0.0) {
+        ctl->flag = FLAG_CONV;
+        ctl->conv_iter = k;
+        return;
+    }
+    if (k >= ctl->max_iter) {
+        ctl->flag = FLAG_MAXIT;
+        ctl->conv_iter = k;
+        return;
+    }
+    if (!(RZ > 0.0) || !isfinite(RZ)) {
+        ctl->flag = FLAG_BREAK;
+        ctl->conv_iter = k;
+        return;
+    }
+    ctl->beta = first ? 0.0 : RZ / ctl->rr;
+    ctl->rr = RZ;
+}
 
 // lane l's value from lane 63 - l
 __device__ inline float lane_reverse(float v, int addr) {
@@ -454,83 +481,19 @@ void k_pc2_solve(Pc2Args<T, NR> a) {
         if (threadIdx.x < 2) {
             double v = 0.0;
             for (int u = 0; u < ni; ++u) v += sRed[u][threadIdx.x];
-            a.partials[(int64_t)2 * h * nblk + 2 * (int64_t)blk + threadIdx.x] = v;
+            st_agent(a.partials + (int64_t)2 * h * nblk + 2 * (int64_t)blk + threadIdx.x, v);
         }
         if (h + 1 < NR) __syncthreads();
     }
-}
-
-// After the SpMV: alpha = (r, z) / (p, q) (or a breakdown); (p, q) is the
-// first of every `stride` partials.
-__global__ __launch_bounds__(kRedThreads) void k_pc2_fin_a(const double *partials, int nblk,
-                                                           int stride, Ctl *ctl) {
-    if (ctl->flag != FLAG_RUN) return;
-    __shared__ double sh[kRedThreads];
-    double v = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kRedThreads) v += partials[(int64_t)b * stride];
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+    // the finalize, by the block that finishes last
+    if (!last_block(a.count, (uint32_t)nblk)) return;
+#pragma unroll
+    for (int h = 0; h < NR; ++h) {
+        if (!run[h]) continue;
+        double S[2];
+        sum_partials<kPc2Threads, 2>(a.partials + (int64_t)2 * h * nblk, nblk, 2, S, &sRed[0][0]);
+        if (threadIdx.x == 0) pc2_beta(a.ctl + h, S[0], S[1], !upd);
     }
-    if (threadIdx.x != 0) return;
-    const double PQ = sh[0];
-    ctl->pq = PQ;
-    ctl->launches += 1;
-    if (!(PQ > 0.0) || !isfinite(PQ)) {
-        ctl->flag = FLAG_BREAK;
-        ctl->conv_iter = ctl->iter;
-        return;
-    }
-    ctl->alpha_prev = ctl->alpha;
-    ctl->alpha = ctl->rr / PQ;
-}
-
-// After the preconditioner solve: (r, z), ||W r||^2, stopping test, beta.
-// ctl->iter counts finished iterations; is_first marks the solve of the
-// initial residual (no iteration finished yet).
-__global__ __launch_bounds__(kRedThreads) void k_pc2_fin_b(const double *partials, int nblk,
-                                                           Ctl *ctl, int is_first) {
-    if (ctl->flag != FLAG_RUN) return;
-    __shared__ double sh[kRedThreads * 2];
-    double v0 = 0.0, v1 = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kRedThreads) {
-        v0 += partials[(int64_t)b * 2];
-        v1 += partials[(int64_t)b * 2 + 1];
-    }
-    sh[threadIdx.x * 2] = v0;
-    sh[threadIdx.x * 2 + 1] = v1;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sh[threadIdx.x * 2] += sh[(threadIdx.x + s) * 2];
-            sh[threadIdx.x * 2 + 1] += sh[(threadIdx.x + s) * 2 + 1];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
-    const double RZ = sh[0], RW = sh[1];
-    const int k = is_first ? ctl->iter : ctl->iter + 1;
-    ctl->iter = k;
-    ctl->rw = RW;
-    if (RW <= ctl->tol2 || RW == 0.0) {
-        ctl->flag = FLAG_CONV;
-        ctl->conv_iter = k;
-        return;
-    }
-    if (k >= ctl->max_iter) {
-        ctl->flag = FLAG_MAXIT;
-        ctl->conv_iter = k;
-        return;
-    }
-    if (!(RZ > 0.0) || !isfinite(RZ)) {
-        ctl->flag = FLAG_BREAK;
-        ctl->conv_iter = k;
-        return;
-    }
-    ctl->beta = is_first ? 0.0 : RZ / ctl->rr;
-    ctl->rr = RZ;
 }
 
 // After a PC2 run: x moves in every second direction launch only, two updates
