@@ -118,10 +118,14 @@ __device__ inline double ld_agent(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sum NV values over the block in a fixed order; the first NV threads write
-// them to out (AGENT: at agent scope, for another block of this launch).
-template <int NV, bool AGENT = false>
-__device__ inline void block_sum_store(double (&v)[NV], double *out, double *lds) {
+// Sum NV values over the block in a fixed order; thread t of the first NV
+// writes value t at agent scope to out[t * nblk], out pointing at this block's
+// entry of the partials.  Partials lie value by value, [NV][nblk], so that the
+// block that sums them reads whole lines (block by block, the loads of a wave
+// touched a line per lane and value: three right-hand sides on 66 x 53 x 112
+// cells 13.9 ms a solve instead of 12.2).
+template <int NV>
+__device__ inline void block_sum_store(double (&v)[NV], double *out, int64_t nblk, double *lds) {
     const int tid = threadIdx.x + threadIdx.y * blockDim.x;
     const int lane = tid & (kWave - 1);
     const int wv = tid / kWave;
@@ -137,35 +141,95 @@ __device__ inline void block_sum_store(double (&v)[NV], double *out, double *lds
     if (tid < NV) {
         double s = 0.0;
         for (int u = 0; u < nw; ++u) s += lds[u * NV + tid];
-        if constexpr (AGENT) st_agent(out + tid, s);
-        else out[tid] = s;
+        st_agent(out + tid * nblk, s);
     }
 }
 
+// Counters of the blocks of a launch that have finished: kCountGroups groups of
+// blocks count in lines of their own and the last block of each group counts
+// in the first line.  Additions to one line take turns: with one counter for
+// all 945 blocks a single-precision iteration on 42 x 69 x 141 cells took 26
+// us, with groups 17.
+constexpr int kCountGroups = 16;  // 8, 32 and 64: the same within 1%
+struct BlockCount {
+    uint32_t n[1 + kCountGroups][16];
+};
+
 // Whether this block is the last of nblk to come here, uniform across the
-// block.  What the block's first wave has stored at agent scope before is then
+// block (blk: its index).  What the block's first wave has stored at agent
+// scope before is then
 // visible, for the last block, to agent-scope loads: the wave waits until its
 // stores have been acknowledged before it counts itself (relaxed: a release
 // would write back the whole L2, which cost the iteration kernel 17% on the
-// 52.4M-cell grid).  *count is zero before the launch and after it.
-__device__ inline bool last_block(uint32_t *count, uint32_t nblk) {
+// 52.4M-cell grid).  The counters are zero before the launch and after it.
+__device__ inline bool last_block(BlockCount *count, uint32_t nblk, uint32_t blk) {
     __shared__ int last;
     const int tid = threadIdx.x + threadIdx.y * blockDim.x;
     if (tid < kWave) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (tid == 0) {
-            const uint32_t n = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            last = n == nblk - 1;
-            if (n == nblk - 1) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            auto add = [](uint32_t *c, uint32_t of) {
+                const bool full = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == of - 1;
+                if (full) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return full;
+            };
+            constexpr uint32_t G = kCountGroups;
+            const uint32_t g = blk % G;
+            last = add(count->n[1 + g], (nblk - g + G - 1) / G) && add(count->n[0], min(nblk, G));
         }
     }
     __syncthreads();
     return last != 0;
 }
 
+// ---------------------------------------------------------------- reports to the host
+// Right-hand sides one iteration kernel can carry (they share the operator).
+constexpr int kMaxRhs = 4;
+
+// What kernels of a solve write into pinned, coherent host memory for the
+// thread that waits there: no copy, event or stream synchronisation stands
+// between a finished iteration and the host.
+struct HostBox {
+    uint64_t progress[kMaxRhs];  // token << 32 | finished iterations << 1 | the run has stopped
+    uint64_t sums_done;          // the token of the sums below
+    double sums[4];
+    uint64_t waited;             // the token of a persistent run that gave up waiting
+    Ctl ctl[kMaxRhs];            // the control block, once stopped
+};
+
+// Where to report (no box: nowhere, the host copies what it wants to see), the
+// token of the wait the report belongs to, and how many iterations (a power of
+// two) pass between two reports of a run under way: the kernel that writes to
+// the host ends about 1 us later for it.
+struct Report {
+    HostBox *box;
+    uint32_t token;
+    int every;
+};
+
+__device__ inline void put_host(uint64_t *p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Control block c as this thread has left it: its progress, and all of it
+// when the run has stopped.
+__device__ inline void report_ctl(Report rep, int c, const Ctl *ctl) {
+    if (!rep.box) return;
+    const bool stopped = ctl->flag != FLAG_RUN;
+    if (!stopped && (ctl->iter & (rep.every - 1)) != 0) return;
+    if (stopped) {
+        static_assert(sizeof(Ctl) % 8 == 0, "copied in words");
+        const uint64_t *from = reinterpret_cast<const uint64_t *>(ctl);
+        uint64_t *to = reinterpret_cast<uint64_t *>(&rep.box->ctl[c]);
+#pragma unroll
+        for (int t = 0; t < (int)(sizeof(Ctl) / 8); ++t) put_host(to + t, from[t]);
+        __threadfence_system();
+    }
+    put_host(&rep.box->progress[c], (uint64_t)rep.token << 32 | (uint32_t)ctl->iter << 1 | (stopped ? 1u : 0u));
+}
+
 // ---------------------------------------------------------------- CG finalize
-// Fixed-order sum of NV partials per block ([nblk][stride], partials pointing
-// at the first of them) over nblk blocks by the NT threads of one block, read
+// Fixed-order sum of NV of the partials (values 0, VS, 2 VS, ... of [][nblk]) over nblk blocks by the NT threads of one block, read
 // at agent scope: thread t adds blocks t, t + NT, ... in order, the waves
 // combine by a butterfly, the wave sums are added in wave order (bitwise
 // reproducible).  Every thread gets the sums.  kSumAhead blocks' partials are
@@ -173,19 +237,20 @@ __device__ inline bool last_block(uint32_t *count, uint32_t nblk) {
 // a time, the persistent run on 32 x 32 x 64 cells took 12.8 instead of 10.6 us
 // per iteration).
 constexpr int kSumAhead = 4;
-template <int NT, int NV>
-__device__ inline void sum_partials(const double *partials, int nblk, int stride, double (&out)[NV],
+template <int NT, int NV, int VS = 1>
+__device__ inline void sum_partials(const double *partials, int nblk, double (&out)[NV],
                                     double *lds) {
     double v[NV];
 #pragma unroll
     for (int t = 0; t < NV; ++t) v[t] = 0.0;
-    for (int b0 = threadIdx.x; b0 < nblk; b0 += NT * kSumAhead) {
+    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+    for (int b0 = tid; b0 < nblk; b0 += NT * kSumAhead) {
         double w[kSumAhead][NV];
 #pragma unroll
         for (int u = 0; u < kSumAhead; ++u) {
             const int b = min(b0 + u * NT, nblk - 1);
 #pragma unroll
-            for (int t = 0; t < NV; ++t) w[u][t] = ld_agent(partials + (int64_t)b * stride + t);
+            for (int t = 0; t < NV; ++t) w[u][t] = ld_agent(partials + (int64_t)t * VS * nblk + b);
         }
 #pragma unroll
         for (int u = 0; u < kSumAhead; ++u)
@@ -196,8 +261,8 @@ __device__ inline void sum_partials(const double *partials, int nblk, int stride
     }
 #pragma unroll
     for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
-    const int wv = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
+    const int wv = tid / kWave;
+    if ((tid & (kWave - 1)) == 0) {
 #pragma unroll
         for (int t = 0; t < NV; ++t) lds[wv * NV + t] = v[t];
     }
@@ -279,10 +344,26 @@ __device__ inline void pcg_finalize(Ctl *ctl, const double (&S)[kNV]) {
     }
 }
 
-// ---------------------------------------------------------------- iteration kernel
-// Right-hand sides one iteration kernel can carry (they share the operator).
-constexpr int kMaxRhs = 4;
+// The NV sums over all blocks' partials ([nblk][NV]), by the last block of a
+// kernel with NT threads: to the host, and to the control block.
+template <int NT, int NV>
+__device__ inline void finish_sums(const double *partials, int nblk, int blk, BlockCount *count, Ctl *ctl,
+                                   Report rep, double *lds) {
+    static_assert(NV <= 4, "HostBox::sums");
+    if (!last_block(count, (uint32_t)nblk, (uint32_t)blk)) return;
+    double S[NV];
+    sum_partials<NT, NV>(partials, nblk, S, lds);
+    if (threadIdx.x != 0 || threadIdx.y != 0) return;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) ctl->sums[t] = S[t];
+    if (!rep.box) return;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) put_host(reinterpret_cast<uint64_t *>(&rep.box->sums[t]), __builtin_bit_cast(uint64_t, S[t]));
+    __threadfence_system();
+    put_host(&rep.box->sums_done, rep.token);
+}
 
+// ---------------------------------------------------------------- iteration kernel
 template <typename T>
 struct IterArgs {
     // per right-hand side
@@ -301,9 +382,10 @@ struct IterArgs {
     // shared
     const T *cr, *ct, *cp;
     const double *w;
-    double *partials;  // [nblk][NR][kNV]
+    double *partials;  // [NR * kNV][nblk]
     Ctl *ctl;          // [NR]
-    uint32_t *count;   // blocks that have finished (last_block)
+    BlockCount *count;
+    Report rep;
     int alpha_only;    // 1: a PC2 direction launch, whose finalize only sets alpha
     Dims d;
     int tiles_i, tiles_k, tiles_j, ti;  // r chunks, phi segments, theta tiles; r planes per chunk
@@ -991,7 +1073,7 @@ __device__ __forceinline__ void pcg_iter_body(const IterArgs<T> &a, const IterSc
         }
     }
     __shared__ double sRed[WPB * NR * kNV];
-    block_sum_store<NR * kNV, true>(acc, a.partials + (int64_t)L * NR * kNV, sRed);
+    block_sum_store<NR * kNV>(acc, a.partials + L, a.nblk, sRed);
 }
 
 // After the SpMV of a PC2 iteration (one thread): alpha = (r, z) / (p, q), or
@@ -1008,6 +1090,17 @@ __device__ inline void pc2_alpha(Ctl *ctl, double PQ) {
     ctl->alpha = ctl->rr / PQ;
 }
 
+// Right-hand side c's sums of S.
+template <int NR>
+__device__ inline void pick_sums(const double (&S)[NR * kNV], int c, double (&out)[kNV]) {
+#pragma unroll
+    for (int t = 0; t < kNV; ++t) {
+        out[t] = S[t];
+#pragma unroll
+        for (int h = 1; h < NR; ++h) out[t] = (c == h) ? S[h * kNV + t] : out[t];
+    }
+}
+
 template <typename T, int NR, int WPB, int RPW, int V, bool HALO>
 __global__ __launch_bounds__(kWave *WPB)
 #if MAS_ITER_WPE > 0
@@ -1017,25 +1110,34 @@ void k_pcg_iter(IterArgs<T> a) {
     IterScalars<T, NR> sc;
     if (!iter_scalars<T, NR>(a.ctl, sc)) return;
     pcg_iter_body<T, NR, WPB, RPW, V, HALO>(a, sc);
-    if (!last_block(a.count, (uint32_t)a.nblk)) return;
+    if (!last_block(a.count, (uint32_t)a.nblk, blockIdx.x)) return;
     // The finalize, by the block that finishes last.  A launch of its own took
     // 4.5 us and a gap per iteration (5 x 3 of them with three PC2 right-hand
     // sides: 12.9 -> 11.9 ms a solve on 96 x 160 x 320 cells; one PC1 solve on
     // 64 x 96 x 192 cells 3.89 -> 3.79 ms; nothing lost on 52.4M cells).
+    // One pass sums all right-hand sides' partials; thread c finalizes
+    // right-hand side c.
     constexpr int NT = kWave * WPB;
-    __shared__ double lds[WPB * kNV];
+    __shared__ double lds[WPB * NR * kNV];
+    const int c = threadIdx.x;
+    if (a.alpha_only) {
+        double S[NR];
+        sum_partials<NT, NR, kNV>(a.partials, a.nblk, S, lds);
+        if (c < NR && a.ctl[c].flag == FLAG_RUN) {
+            double pq = S[0];
 #pragma unroll
-    for (int c = 0; c < NR; ++c) {
-        if (!sc.run[c]) continue;  // uniform
-        const double *part = a.partials + c * kNV;
-        if (a.alpha_only) {
-            double S[1];
-            sum_partials<NT, 1>(part, a.nblk, NR * kNV, S, lds);
-            if (threadIdx.x == 0) pc2_alpha(a.ctl + c, S[0]);
-        } else {
-            double S[kNV];
-            sum_partials<NT, kNV>(part, a.nblk, NR * kNV, S, lds);
-            if (threadIdx.x == 0) pcg_finalize(a.ctl + c, S);
+            for (int h = 1; h < NR; ++h) pq = (c == h) ? S[h] : pq;
+            pc2_alpha(a.ctl + c, pq);
+            if (a.ctl[c].flag != FLAG_RUN) report_ctl(a.rep, c, a.ctl + c);
+        }
+    } else {
+        double S[NR * kNV];
+        sum_partials<NT, NR * kNV>(a.partials, a.nblk, S, lds);
+        if (c < NR && a.ctl[c].flag == FLAG_RUN) {
+            double Sc[kNV];
+            pick_sums<NR>(S, c, Sc);
+            pcg_finalize(a.ctl + c, Sc);
+            report_ctl(a.rep, c, a.ctl + c);
         }
     }
 }
@@ -1057,14 +1159,14 @@ void k_pcg_iter(IterArgs<T> a) {
 struct PersistSync {
     uint32_t bar;    // barrier arrivals, zero at launch
     int32_t err;     // 1: a block gave up waiting at a barrier
-    uint32_t count;  // blocks of a launch that have finished (last_block)
+    BlockCount count;
 };
 
 template <typename T, int NR>
 struct PersistArgs {
     IterArgs<T> it;                   // shared fields; buffers and partials set per iteration
     T *r[NR][2], *p[NR][2], *q[NR][2];  // by parity: iteration k reads index k & 1
-    double *partials[2];              // by parity, [nblk][NR][kNV] each
+    double *partials[2];              // by parity, [NR * kNV][nblk] each
     Ctl *ctl;                         // [NR] (k_run_init has set them)
     PersistSync *sync;
     int iter0;                        // the run's first iteration index
@@ -1103,7 +1205,7 @@ template <typename T, int NR, int WPB, int RPW, int V>
 __global__ __launch_bounds__(kWave *WPB) void k_pcg_persist(PersistArgs<T, NR> a) {
     static_assert(kWave * WPB == kRedThreads, "one block sums the partials");
     __shared__ Ctl lc[NR];  // this block's copies of the control blocks
-    __shared__ double lds[(kRedThreads / kWave) * kNV];
+    __shared__ double lds[(kRedThreads / kWave) * NR * kNV];
     if (threadIdx.x < NR) lc[threadIdx.x] = a.ctl[threadIdx.x];
     __syncthreads();
     IterArgs<T> it = a.it;
@@ -1132,22 +1234,30 @@ __global__ __launch_bounds__(kWave *WPB) void k_pcg_persist(PersistArgs<T, NR> a
         it.xstep = (s >= 2 && (s & 1) == 0) ? 1 : 0;
         pcg_iter_body<T, NR, WPB, RPW, V, false>(it, sc);
         if (!grid_barrier(a.sync, (uint32_t)(s + 1) * gridDim.x, a.wait_ticks)) {
-            if (threadIdx.x == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0) {
+                __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (a.it.rep.box) put_host(&a.it.rep.box->waited, a.it.rep.token);
+            }
             return;
         }
+        {
+            double S[NR * kNV];
+            sum_partials<kRedThreads, NR * kNV>(it.partials, it.nblk, S, lds);
+            const int c = threadIdx.x;
+            if (c < NR && lc[c].flag == FLAG_RUN) {
+                double Sc[kNV];
+                pick_sums<NR>(S, c, Sc);
+                pcg_finalize(&lc[c], Sc);
+                if (blockIdx.x == 0) {
+                    a.ctl[c] = lc[c];
+                    if (lc[c].flag != FLAG_RUN) report_ctl(a.it.rep, c, &lc[c]);
+                }
+            }
+        }
+        __syncthreads();
         bool any = false;
 #pragma unroll
-        for (int c = 0; c < NR; ++c) {
-            if (lc[c].flag != FLAG_RUN) continue;  // uniform: every thread reads the same flag
-            double S[kNV];
-            sum_partials<kRedThreads, kNV>(it.partials + c * kNV, it.nblk, NR * kNV, S, lds);
-            if (threadIdx.x == 0) {
-                pcg_finalize(&lc[c], S);
-                if (blockIdx.x == 0) a.ctl[c] = lc[c];
-            }
-            __syncthreads();
-            any = any || lc[c].flag == FLAG_RUN;
-        }
+        for (int c = 0; c < NR; ++c) any = any || lc[c].flag == FLAG_RUN;
         if (!any) return;
     }
 }
@@ -1182,24 +1292,6 @@ __global__ __launch_bounds__(256) void k_x_catchup(CatchupArgs<T> a) {
         x[i] = x[i] + al * p[i];
 }
 
-// Generic fixed-order sum of [nblk][nv] partials into ctl->sums[0:nv].
-__global__ __launch_bounds__(kRedThreads) void k_reduce(const double *partials, int nblk, int nv,
-                                                       Ctl *ctl) {
-    __shared__ double sh[kRedThreads];
-    for (int t = 0; t < nv; ++t) {
-        double v = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kRedThreads) v += partials[(int64_t)b * nv + t];
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) ctl->sums[t] = sh[0];
-        __syncthreads();
-    }
-}
-
 // Reset the control blocks and the counters for a new PCG run of n right-hand
 // sides (a kernel, not a memset, so it is safe inside captured graphs as well).
 // flag0 = FLAG_RUN starts the run; another flag leaves this control block
@@ -1214,7 +1306,9 @@ struct RunInit {
 };
 
 __global__ void k_run_init(Ctl *ctl_all, PersistSync *sync, RunInit in) {
-    if (threadIdx.x == 0) *sync = PersistSync{0u, 0, 0u};
+    for (int t = threadIdx.x; t < (int)(sizeof(PersistSync) / 4); t += blockDim.x)
+        reinterpret_cast<uint32_t *>(sync)[t] = 0u;
+    // n = 0: only this
     if ((int)threadIdx.x >= in.n) return;
     const int c = threadIdx.x;
     Ctl *ctl = ctl_all + c;
@@ -1602,7 +1696,10 @@ constexpr int kReLoads = (kRePR * kRePC + kReThreads - 1) / kReThreads;
 struct ResArgs {
     const double *bhat, *xhat, *w, *cr, *ct, *cp;
     Dims d;
-    double *partials;  // [nblk][2]
+    double *partials;  // [2][nblk]
+    BlockCount *count;
+    Ctl *ctl;          // receives the sums
+    Report rep;
     int tiles_i, tiles_k, tiles_j, ti, nblk;
 };
 
@@ -1749,7 +1846,8 @@ __global__ __launch_bounds__(kReThreads) void k_residual(ResArgs a, TOUT *rout) 
         __syncthreads();
     }
     __shared__ double lds[kReWaves * 2];
-    block_sum_store<2>(acc, a.partials + 2 * (int64_t)blockIdx.x, lds);
+    block_sum_store<2>(acc, a.partials + blockIdx.x, a.nblk, lds);
+    finish_sums<kReThreads, 2>(a.partials, a.nblk, blockIdx.x, a.count, a.ctl, a.rep, lds);
 }
 
 // b^ = V src / w (src = rhs) or src / w (src = adjoint seed); x^ = w x0
@@ -1761,7 +1859,8 @@ template <typename TOUT>
 __global__ __launch_bounds__(kWave *kSimpleJ) void k_setup(const double *src, int src_is_rhs,
                                                            const double *w, Geo geo, Dims d,
                                                            double *bhat, double *x, int use_x0,
-                                                           TOUT *rout, double *partials) {
+                                                           TOUT *rout, double *partials,
+                                                           BlockCount *count, Ctl *ctl, Report rep) {
     static_assert(kSimpleNV >= 3, "partials per simple block");
     __shared__ double lds[kSimpleJ * 3];
     double acc[3] = {0.0, 0.0, 0.0};
@@ -1783,7 +1882,9 @@ __global__ __launch_bounds__(kWave *kSimpleJ) void k_setup(const double *src, in
             }
         }
     })
-    block_sum_store<3>(acc, partials + 3 * simple_block_id(), lds);
+    const int nblk = (int)(gridDim.x * gridDim.y * gridDim.z), blk = (int)simple_block_id();
+    block_sum_store<3>(acc, partials + blk, nblk, lds);
+    finish_sums<kWave * kSimpleJ, 3>(partials, nblk, blk, count, ctl, rep, lds);
 }
 
 // x = x^ / w, in place.

@@ -580,22 +580,33 @@ extern "C" int64_t mas_pcg_multi_workspace_bytes(const mas_op *op, int32_t nrhs)
 // ------------------------------------------------------------------ drivers
 namespace {
 
+// One box per host thread: a call waits for its solve, so a thread has one
+// solve under way at a time.  A token marks each wait, so that a report meant
+// for an earlier one is not taken for it.
 struct Pinned {
-    int32_t *p = nullptr;
+    HostBox *p = nullptr;
+    uint32_t token = 0;
     ~Pinned() {
         if (p) (void)hipHostFree(p);
     }
 };
 static thread_local Pinned g_pinned;
 
-static int pinned_buffer(int32_t **out) {
+static int pinned_box(HostBox **out) {
     if (!g_pinned.p) {
         void *p = nullptr;
-        HIPCHK(hipHostMalloc(&p, 4096, hipHostMallocDefault));
-        g_pinned.p = static_cast<int32_t *>(p);
+        HIPCHK(hipHostMalloc(&p, sizeof(HostBox), hipHostMallocCoherent));
+        std::memset(p, 0, sizeof(HostBox));
+        g_pinned.p = static_cast<HostBox *>(p);
     }
     *out = g_pinned.p;
     return MAS_OK;
+}
+
+static Report new_report(HostBox *box) {
+    if (!box) return Report{nullptr, 0u, 1};
+    if (++g_pinned.token == 0u) ++g_pinned.token;
+    return Report{box, g_pinned.token, 1};
 }
 
 struct Ctx {
@@ -604,7 +615,8 @@ struct Ctx {
     Ctl *ctl;  // [nrhs]; ctl[0] also receives k_reduce sums
     double *partials;
     bool timing;
-    bool no_alloc = false;  // allocation-free entry point: no pinned buffer, no events
+    bool no_alloc = false;  // allocation-free entry point: no pinned box, no events
+    HostBox *box = nullptr; // where kernels report (null: no_alloc)
     int chunk = 0;          // r planes per chunk of the iteration kernel (0: automatic)
     PersistSync *sync = nullptr;     // barrier words of the persistent launch
     int launch = MAS_LAUNCH_AUTO;    // requested launch mode of PC1 runs
@@ -624,74 +636,142 @@ static int read_ctl(Ctx &cx, Ctl *h, int c = 0) {
     return MAS_OK;
 }
 
-// Host polling of the run flags of control blocks ctl[0:n] after each batch
-// of launches.  Normally one batch behind: the flags are copied into a pinned
-// buffer behind the batch and the host waits for the previous batch's event,
-// so the device queue never runs dry.  For the allocation-free entry point
-// (no pinned buffer, no events) the flags are copied synchronously after
-// each batch.
-struct FlagPoll {
-    Ctx &cx;
-    int32_t *pin = nullptr;
-    hipEvent_t done[2] = {nullptr, nullptr};
-    int nb = 0;  // batches polled
-    explicit FlagPoll(Ctx &c) : cx(c) {}
-    ~FlagPoll() {
-        for (auto e : done)
-            if (e) (void)hipEventDestroy(e);
+// Wait for a report in the pinned box (done() turns true).  The stream is
+// asked now and then, so that a call whose kernels have failed, or have all
+// ended without the report, ends with an error.
+template <typename F>
+static int wait_report(Ctx &cx, F done) {
+    for (uint32_t n = 1;; ++n) {
+        if (done()) return MAS_OK;
+        if ((n & 1023u) == 0u) {
+            const hipError_t e = hipStreamQuery(cx.stream);
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();
+            } else {
+                if (done()) return MAS_OK;
+                HIPCHK(e);
+                return fail(MAS_EHIP, "internal: a kernel ended without its report");
+            }
+        }
+        __builtin_ia32_pause();
     }
-    int init() {
-        if (cx.no_alloc) return MAS_OK;
-        int e = pinned_buffer(&pin);
+}
+
+// Start of a call on its workspace: the box, and zeroed counters.
+static int begin_call(Ctx &cx) {
+    if (!cx.no_alloc) {
+        const int e = pinned_box(&cx.box);
         if (e != MAS_OK) return e;
-        HIPCHK(hipEventCreateWithFlags(&done[0], hipEventDisableTiming));
-        HIPCHK(hipEventCreateWithFlags(&done[1], hipEventDisableTiming));
+    }
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(256), 0, cx.stream, cx.ctl, cx.sync, RunInit{});
+    LAUNCHCHK();
+    return MAS_OK;
+}
+
+// Sums a kernel has formed (finish_sums) under report rep.
+static int get_sums(Ctx &cx, Report rep, int nv, double *out) {
+    if (!rep.box) {
+        HIPCHK(hipMemcpyAsync(out, &cx.ctl->sums[0], nv * sizeof(double), hipMemcpyDeviceToHost,
+                              cx.stream));
+        HIPCHK(hipStreamSynchronize(cx.stream));
         return MAS_OK;
     }
-    // Call after enqueueing a batch; *stop becomes true once every flag seen
-    // has left FLAG_RUN.
-    int after_batch(int n, bool *stop) {
-        if (cx.no_alloc) {
+    const int e = wait_report(cx, [&] { return __atomic_load_n(&rep.box->sums_done, __ATOMIC_ACQUIRE) == rep.token; });
+    if (e != MAS_OK) return e;
+    for (int t = 0; t < nv; ++t) out[t] = rep.box->sums[t];
+    return MAS_OK;
+}
+
+struct PcgResult {
+    int flag[kMaxRhs];
+    int last_iter[kMaxRhs];  // index of the last iteration kernel that did work
+    Ctl ctl[kMaxRhs];        // the control blocks at the end (active right-hand sides)
+};
+
+// The host's side of one run of launched iterations: how far the device has
+// come, and so how many iterations may be queued ahead of it.  Launches queued
+// past the end of a run find it stopped and do nothing, at 2-7 us each
+// (batches of 16 with the flags copied one batch behind queued up to 32
+// iterations past the end: half of a PC2 solve's launches on 61 x 93 x 187
+// cells), while too few let the device run dry when the host is late: kAhead
+// launches of 10 us and more, reported every kEvery, cover the host's 4 us per
+// launch and short delays.  96 x 160 x 320 cells, three PC2 right-hand sides:
+// 12.28 -> 11.57 ms a solve; 61 x 93 x 187, PC2: 2.72 -> 2.61; 16 x 16 x 32,
+// forward and backward: 1.94 -> 1.69; 12 / 4 and 32 / 16 launches within 1%.
+// For the allocation-free entry point (no box) the flags are copied after
+// every kBatch iterations.
+struct RunWatch {
+    static constexpr int kAhead = 16, kEvery = 8, kBatch = 16;
+    Ctx &cx;
+    int n;               // right-hand sides
+    const bool *active;
+    int launches;        // per iteration
+    Report rep{nullptr, 0u, 1};
+    int seen;            // finished iterations
+    bool stop = false;   // every active right-hand side has stopped
+    RunWatch(Ctx &c, int n_, const bool *a, int iter0, int per) : cx(c), n(n_), active(a), launches(per), seen(iter0) {
+        rep = new_report(c.box);
+        rep.every = kEvery / launches;
+    }
+    void look() {
+        bool all = true;
+        for (int h = 0; h < n; ++h) {
+            if (!active[h]) continue;
+            const uint64_t v = __atomic_load_n(&rep.box->progress[h], __ATOMIC_ACQUIRE);
+            if ((uint32_t)(v >> 32) != rep.token) {
+                all = false;
+                continue;
+            }
+            if (v & 1u) continue;
+            all = false;
+            seen = std::max(seen, (int)((uint32_t)v >> 1));
+        }
+        stop = all;
+    }
+    // before iteration k is queued: waits while enough are
+    int room(int k, int iter0) {
+        if (!rep.box) {
+            if (k == iter0 || (k - iter0) % kBatch != 0) return MAS_OK;
             int32_t fl[kMaxRhs];
             for (int h = 0; h < n; ++h)
-                HIPCHK(hipMemcpyAsync(fl + h, &cx.ctl[h].flag, sizeof(int32_t),
-                                      hipMemcpyDeviceToHost, cx.stream));
+                HIPCHK(hipMemcpyAsync(fl + h, &cx.ctl[h].flag, sizeof(int32_t), hipMemcpyDeviceToHost, cx.stream));
             HIPCHK(hipStreamSynchronize(cx.stream));
-            bool any = false;
-            for (int h = 0; h < n; ++h) any = any || fl[h] == FLAG_RUN;
-            *stop = !any;
-            ++nb;
+            stop = true;
+            for (int h = 0; h < n; ++h) stop = stop && fl[h] != FLAG_RUN;
             return MAS_OK;
         }
-        int32_t *slot = pin + kMaxRhs * (nb & 1);
-        for (int h = 0; h < n; ++h)
-            HIPCHK(hipMemcpyAsync(slot + h, &cx.ctl[h].flag, sizeof(int32_t),
-                                  hipMemcpyDeviceToHost, cx.stream));
-        HIPCHK(hipEventRecord(done[nb & 1], cx.stream));
-        if (nb > 0) {
-            HIPCHK(hipEventSynchronize(done[(nb - 1) & 1]));
-            const int32_t *prev = pin + kMaxRhs * ((nb - 1) & 1);
-            bool any = false;
-            for (int h = 0; h < n; ++h) any = any || prev[h] == FLAG_RUN;
-            if (!any) *stop = true;
+        look();
+        if (stop || (k - seen) * launches < kAhead) return MAS_OK;
+        return wait_report(cx, [&] {
+            look();
+            return stop || (k - seen) * launches < kAhead;
+        });
+    }
+    // after the last launch of the run
+    int finish(PcgResult *res) {
+        if (rep.box) {
+            const int e = wait_report(cx, [&] {
+                if (!stop) look();
+                return stop;
+            });
+            if (e != MAS_OK) return e;
         }
-        ++nb;
+        for (int h = 0; h < n; ++h) {
+            if (!active[h] || !rep.box) {
+                const int e = rep.box ? MAS_OK : read_ctl(cx, &res->ctl[h], h);
+                if (e != MAS_OK) return e;
+                if (!active[h]) res->ctl[h].flag = FLAG_CONV, res->ctl[h].conv_iter = -1;
+            } else {
+                res->ctl[h] = rep.box->ctl[h];
+            }
+            res->flag[h] = res->ctl[h].flag;
+            res->last_iter[h] = res->flag[h] == FLAG_RUN ? res->ctl[h].iter - 1 : res->ctl[h].conv_iter;
+        }
+        // event samples may still be under way
+        if (cx.timing) HIPCHK(hipStreamSynchronize(cx.stream));
         return MAS_OK;
     }
 };
-
-// Sum nv values of the simple-kernel partials into ctl->sums[0:nv] and
-// copy them to the host (synchronous).
-static int reduce_n(Ctx &cx, int nv, double *out, int nblk = -1) {
-    if (nblk < 0) nblk = (int)cx.op->s.nblk_simple();
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kRedThreads), 0, cx.stream, cx.partials, nblk, nv,
-                       cx.ctl);
-    LAUNCHCHK();
-    HIPCHK(hipMemcpyAsync(out, &cx.ctl->sums[0], nv * sizeof(double), hipMemcpyDeviceToHost,
-                          cx.stream));
-    HIPCHK(hipStreamSynchronize(cx.stream));
-    return MAS_OK;
-}
 
 // r^ = b^ - A^ x^ in double precision, stored as T into r.
 // Returns rw2 = ||W r^||^2 = ||b - A x||^2 and rr2 = ||r^||^2.
@@ -701,7 +781,7 @@ static int residual(Ctx &cx, const double *bhat, const double *xhat, T *r, doubl
     const mas_op *op = cx.op;
     const Shape &s = op->s;
     ResArgs ra{bhat, xhat, op->w, op->c64[0], op->c64[1], op->c64[2], s.dims(), cx.partials,
-               0, 0, 0, 0, 0};
+               &cx.sync->count, cx.ctl, new_report(cx.box), 0, 0, 0, 0, 0};
     ra.tiles_k = (s.np + kReC - 1) / kReC;
     ra.tiles_j = (s.nt + kReR - 1) / kReR;
     ra.ti = s.chunk_for((int64_t)ra.tiles_k * ra.tiles_j);
@@ -714,7 +794,7 @@ static int residual(Ctx &cx, const double *bhat, const double *xhat, T *r, doubl
     hipLaunchKernelGGL(k_residual<T>, dim3((unsigned)nblk), dim3(kReThreads), 0, cx.stream, ra, r);
     LAUNCHCHK();
     double sums[2];
-    int st = reduce_n(cx, 2, sums, ra.nblk);
+    int st = get_sums(cx, ra.rep, 2, sums);
     *rw2 = sums[0];
     if (rr2) *rr2 = sums[1];
     return st;
@@ -736,11 +816,6 @@ struct RhsSet {
     // p[h][iter0 % 2] with p = r + beta0 p (keep_p), or starts with p = r
     bool keep_p[kMaxRhs] = {false, false, false, false};
     double beta0[kMaxRhs] = {0.0, 0.0, 0.0, 0.0};
-};
-
-struct PcgResult {
-    int flag[kMaxRhs];
-    int last_iter[kMaxRhs];  // index of the last iteration kernel that did work
 };
 
 constexpr int64_t kCatchupBlocks = 8192;  // grid-stride blocks of k_x_catchup
@@ -834,7 +909,12 @@ static void start_run(Ctx &cx, const RhsSet<T> &v, int mode, int iter0, int chec
         in.tol2[h] = v.tol2[h];
         in.beta0[h] = v.keep_p[h] ? v.beta0[h] : 0.0;
     }
-    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(kWave), 0, cx.stream, cx.ctl, cx.sync, in);
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(256), 0, cx.stream, cx.ctl, cx.sync, in);
+}
+
+static int persist_gave_up() {
+    return fail(MAS_EHIP, "persistent PCG run: a block waited more than %g s at a grid barrier",
+                kPersistWaitSec);
 }
 
 // A PC1 run of NR right-hand sides in one cooperative launch of
@@ -850,6 +930,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     for (int h = 0; h < NR; ++h) work = work || (v.active[h] && v.max_iter[h] >= iter0);
     start_run<T, NR>(cx, v, mode, iter0, check_every);
     LAUNCHCHK();
+    RunWatch watch(cx, NR, v.active, iter0, 1);
     cx.launched = MAS_LAUNCH_PERSISTENT;
     if (work) {
         PersistArgs<T, NR> pa{};
@@ -868,6 +949,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         a.ti = s.ti(V, ch);
         a.nblk = (int)s.nblk_iter(V, ch);
         a.records = 0;
+        a.rep = watch.rep;
         for (int h = 0; h < NR; ++h) {
             a.x[h] = v.x[h];
             for (int t = 0; t < 2; ++t) {
@@ -892,20 +974,24 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     }
     int e = launch_catchup<T, NR>(cx, v, iter0);
     if (e != MAS_OK) return e;
-    PersistSync hs{};
-    HIPCHK(hipMemcpyAsync(&hs, cx.sync, sizeof hs, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipStreamSynchronize(st));
-    if (hs.err)
-        return fail(MAS_EHIP, "persistent PCG run: a block waited more than %g s at a grid barrier",
-                    kPersistWaitSec);
-    for (int h = 0; h < NR; ++h) {
-        Ctl hc;
-        e = read_ctl(cx, &hc, h);
+    if (watch.rep.box && work) {
+        e = wait_report(cx, [&] {
+            watch.look();
+            return watch.stop || __atomic_load_n(&cx.box->waited, __ATOMIC_ACQUIRE) == watch.rep.token;
+        });
         if (e != MAS_OK) return e;
-        res->flag[h] = hc.flag;
-        res->last_iter[h] = (hc.flag == FLAG_RUN) ? v.max_iter[h] : hc.conv_iter;
+        if (!watch.stop) {
+            HIPCHK(hipStreamSynchronize(st));
+            return persist_gave_up();
+        }
+    } else {
+        PersistSync hs{};
+        HIPCHK(hipMemcpyAsync(&hs, cx.sync, sizeof hs, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        if (hs.err) return persist_gave_up();
+        watch.rep.box = nullptr;  // no kernel ran, or none could report
     }
-    return MAS_OK;
+    return watch.finish(res);
 }
 
 // PCG iterations on the scaled system in precision T for NR right-hand sides
@@ -933,10 +1019,7 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
         if (v.active[h]) max_iter = std::max(max_iter, v.max_iter[h]);
     start_run<T, NR>(cx, v, mode, iter0, check_every);
     LAUNCHCHK();
-    FlagPoll poll(cx);
-    int e = poll.init();
-    if (e != MAS_OK) return e;
-
+    RunWatch watch(cx, NR, v.active, iter0, 1);
     IterArgs<T> a{};
     a.cr = c[0];
     a.ct = c[1];
@@ -945,6 +1028,7 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     a.partials = cx.partials;
     a.ctl = cx.ctl;
     a.count = &cx.sync->count;
+    a.rep = watch.rep;
     a.d = s.dims();
     const int V = iter_vec<T>(s.np, NR);
     a.tiles_i = s.tiles_i(V, cx.chunk);
@@ -957,77 +1041,63 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     const bool use_halo = v.records;
     const dim3 grid((unsigned)a.nblk), block(kWave * kTJ);
 
-    // batches of launches; the host polls the device flags one batch behind
-    const int batch = std::max(check_every, 16);
-    int k = iter0;
-    bool stop = false;
-    while (!stop && k <= max_iter) {
-        const int kend = std::min(max_iter, k + batch - 1);
-        for (; k <= kend; ++k) {
-            const int cur = k & 1, nxt = cur ^ 1;
-            for (int h = 0; h < NR; ++h) {
-                a.r_in[h] = v.r[h][cur];
-                // the first kernel of a run has alpha = 0 (and beta = 0 unless
-                // the direction is kept): point q (and p) at r, finite
-                // values, so that every load stays unconditional
-                a.p_in[h] = (k == iter0 && !v.keep_p[h]) ? v.r[h][cur] : v.p[h][cur];
-                a.q_in[h] = (k == iter0) ? v.r[h][cur] : v.q[h][cur];
-                a.r_out[h] = v.r[h][nxt];
-                a.p_out[h] = v.p[h][nxt];
-                a.q_out[h] = v.q[h][nxt];
-                a.halo_in[h] = v.halo[h][cur];
-                a.halo_out[h] = v.halo[h][nxt];
-            }
-            // the first kernel of a run reads its edge cells directly (no
-            // kernel wrote records for its input); later ones read records
-            const bool halo = use_halo && k != iter0;
-            // x moves in the even launches of the run from the third on (the
-            // first applies alpha = 0)
-            a.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
-            // timing samples: 8 consecutive launches of every 16, so that
-            // launches with and without the x update and the check launches
-            // (every check_every-th) enter in their proportions
-            const bool sample = cx.timing && ((k / 8) & 1) == 1 && cx.ev.size() < 512;
-            if (sample) {
-                hipEvent_t e0, e1;
-                HIPCHK(hipEventCreate(&e0));
-                HIPCHK(hipEventCreate(&e1));
-                cx.ev.push_back(e0);
-                cx.ev.push_back(e1);
-                cx.ev_iter.push_back(k);
-                HIPCHK(hipEventRecord(e0, st));
-            }
-            constexpr int VW = vec_full<T>();
-            auto go = [&](auto vw, auto hl) {
-                hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, decltype(vw)::value,
-                                               decltype(hl)::value>),
-                                   grid, block, 0, st, a);
-            };
-            using F = std::false_type;
-            using Tr = std::true_type;
-            using IW = std::integral_constant<int, VW>;
-            using I1 = std::integral_constant<int, 1>;
-            if (V == VW)
-                halo ? go(IW{}, Tr{}) : go(IW{}, F{});
-            else
-                halo ? go(I1{}, Tr{}) : go(I1{}, F{});
-            if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
+    for (int k = iter0; k <= max_iter; ++k) {
+        int e = watch.room(k, iter0);
+        if (e != MAS_OK) return e;
+        if (watch.stop) break;
+        const int cur = k & 1, nxt = cur ^ 1;
+        for (int h = 0; h < NR; ++h) {
+            a.r_in[h] = v.r[h][cur];
+            // the first kernel of a run has alpha = 0 (and beta = 0 unless
+            // the direction is kept): point q (and p) at r, finite
+            // values, so that every load stays unconditional
+            a.p_in[h] = (k == iter0 && !v.keep_p[h]) ? v.r[h][cur] : v.p[h][cur];
+            a.q_in[h] = (k == iter0) ? v.r[h][cur] : v.q[h][cur];
+            a.r_out[h] = v.r[h][nxt];
+            a.p_out[h] = v.p[h][nxt];
+            a.q_out[h] = v.q[h][nxt];
+            a.halo_in[h] = v.halo[h][cur];
+            a.halo_out[h] = v.halo[h][nxt];
         }
+        // the first kernel of a run reads its edge cells directly (no
+        // kernel wrote records for its input); later ones read records
+        const bool halo = use_halo && k != iter0;
+        // x moves in the even launches of the run from the third on (the
+        // first applies alpha = 0)
+        a.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
+        // timing samples: 8 consecutive launches of every 16, so that
+        // launches with and without the x update and the check launches
+        // (every check_every-th) enter in their proportions
+        const bool sample = cx.timing && ((k / 8) & 1) == 1 && cx.ev.size() < 512;
+        if (sample) {
+            hipEvent_t e0, e1;
+            HIPCHK(hipEventCreate(&e0));
+            HIPCHK(hipEventCreate(&e1));
+            cx.ev.push_back(e0);
+            cx.ev.push_back(e1);
+            cx.ev_iter.push_back(k);
+            HIPCHK(hipEventRecord(e0, st));
+        }
+        constexpr int VW = vec_full<T>();
+        auto go = [&](auto vw, auto hl) {
+            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, decltype(vw)::value,
+                                           decltype(hl)::value>),
+                               grid, block, 0, st, a);
+        };
+        using F = std::false_type;
+        using Tr = std::true_type;
+        using IW = std::integral_constant<int, VW>;
+        using I1 = std::integral_constant<int, 1>;
+        if (V == VW)
+            halo ? go(IW{}, Tr{}) : go(IW{}, F{});
+        else
+            halo ? go(I1{}, Tr{}) : go(I1{}, F{});
+        if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
         LAUNCHCHK();
-        e = poll.after_batch(NR, &stop);
-        if (e != MAS_OK) return e;
     }
-    e = launch_catchup<T, NR>(cx, v, iter0);
+    const int e = launch_catchup<T, NR>(cx, v, iter0);
     if (e != MAS_OK) return e;
-    HIPCHK(hipStreamSynchronize(st));
-    for (int h = 0; h < NR; ++h) {
-        Ctl hc;
-        e = read_ctl(cx, &hc, h);
-        if (e != MAS_OK) return e;
-        res->flag[h] = hc.flag;
-        res->last_iter[h] = (hc.flag == FLAG_RUN) ? v.max_iter[h] : hc.conv_iter;
-    }
-    return MAS_OK;
+    return watch.finish(res);
 }
 
 static void timing_summary(Ctx &cx, int last_iter, mas_pcg_info *info) {
@@ -1103,14 +1173,16 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
         in.tol2[h] = tol2[h];
         if (active[h]) kmax = std::max(kmax, max_iter[h]);
     }
-    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(kWave), 0, st, cx.ctl, cx.sync, in);
+    hipLaunchKernelGGL(k_run_init, dim3(1), dim3(256), 0, st, cx.ctl, cx.sync, in);
     const T *cc[3];
     if constexpr (std::is_same<T, float>::value) {
         for (int t = 0; t < 3; ++t) cc[t] = op->c32[t];
     } else {
         for (int t = 0; t < 3; ++t) cc[t] = op->c64[t];
     }
+    RunWatch watch(cx, NR, active, iter0, 2);
     Pc2Args<T, NR> a{};
+    a.rep = watch.rep;
     a.cr = cc[0];
     a.ct = cc[1];
     a.cp = cc[2];
@@ -1131,6 +1203,7 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     it.partials = cx.partials;
     it.ctl = cx.ctl;
     it.count = &cx.sync->count;
+    it.rep = watch.rep;
     it.alpha_only = 1;
     it.d = s.dims();
     const int V = iter_vec<T>(s.np, NR);
@@ -1155,44 +1228,37 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     // z = M^-1 r of the initial residuals, (r, z), the stopping tests
     solve_all(1);
     LAUNCHCHK();
-    FlagPoll poll(cx);
-    int e = poll.init();
-    if (e != MAS_OK) return e;
     constexpr int VW = vec_full<T>();
     const dim3 igrid((unsigned)it.nblk), iblock(kWave * kTJ);
-    int k = iter0;
-    bool stop = false;
-    while (!stop && k < kmax) {
-        const int kend = std::min(kmax, k + 16);
-        for (; k < kend; ++k) {
-            const bool sample = cx.timing && (k % 16 == 7) && cx.ev.size() < 128;
-            if (sample) {
-                hipEvent_t e0, e1;
-                HIPCHK(hipEventCreate(&e0));
-                HIPCHK(hipEventCreate(&e1));
-                cx.ev.push_back(e0);
-                cx.ev.push_back(e1);
-                cx.ev_iter.push_back(k + 1);
-                HIPCHK(hipEventRecord(e0, st));
-            }
-            for (int h = 0; h < NR; ++h) {
-                // the first direction is z itself (beta = 0): p_old points at z
-                it.p_in[h] = (k == iter0) ? v.z[h] : v.p[h][k & 1];
-                it.p_out[h] = v.p[h][(k + 1) & 1];
-            }
-            it.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
-            if (V == VW)
-                hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, VW, false>), igrid, iblock,
-                                   0, st, it);
-            else
-                hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, 1, false>), igrid, iblock,
-                                   0, st, it);
-            solve_all(0);
-            if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
-        }
-        LAUNCHCHK();
-        e = poll.after_batch(NR, &stop);
+    for (int k = iter0; k < kmax; ++k) {
+        const int e = watch.room(k, iter0);
         if (e != MAS_OK) return e;
+        if (watch.stop) break;
+        const bool sample = cx.timing && (k % 16 == 7) && cx.ev.size() < 128;
+        if (sample) {
+            hipEvent_t e0, e1;
+            HIPCHK(hipEventCreate(&e0));
+            HIPCHK(hipEventCreate(&e1));
+            cx.ev.push_back(e0);
+            cx.ev.push_back(e1);
+            cx.ev_iter.push_back(k + 1);
+            HIPCHK(hipEventRecord(e0, st));
+        }
+        for (int h = 0; h < NR; ++h) {
+            // the first direction is z itself (beta = 0): p_old points at z
+            it.p_in[h] = (k == iter0) ? v.z[h] : v.p[h][k & 1];
+            it.p_out[h] = v.p[h][(k + 1) & 1];
+        }
+        it.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
+        if (V == VW)
+            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, VW, false>), igrid, iblock,
+                               0, st, it);
+        else
+            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, 1, false>), igrid, iblock,
+                               0, st, it);
+        solve_all(0);
+        if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
+        LAUNCHCHK();
     }
     // the x updates the last launches left
     {
@@ -1208,15 +1274,7 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
         hipLaunchKernelGGL(k_pc2_catchup<T>, dim3((unsigned)cblk, NR), dim3(256), 0, st, ca);
         LAUNCHCHK();
     }
-    HIPCHK(hipStreamSynchronize(st));
-    for (int h = 0; h < NR; ++h) {
-        Ctl hc;
-        e = read_ctl(cx, &hc, h);
-        if (e != MAS_OK) return e;
-        res->flag[h] = hc.flag;
-        res->last_iter[h] = (hc.flag == FLAG_RUN) ? max_iter[h] : hc.conv_iter;
-    }
-    return MAS_OK;
+    return watch.finish(res);
 }
 
 // Record buffers of right-hand side h from the workspace layout.
@@ -1273,17 +1331,22 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
     // b^ = W^-1 b, x^ = W x0 or 0, ||b||^2; from x^ = 0 also r^0 = b^ (into
     // the first residual vector, in the working precision) and its norms
     const bool single = o.precision == MAS_FP32_REFINED;
+    st = begin_call(cx);
+    if (st != MAS_OK) return st;
+    const Report srep = new_report(cx.box);
     if (single)
         hipLaunchKernelGGL(k_setup<float>, sgrid, sblock, 0, cx.stream, src, src_is_rhs, op->w,
                            op->geo, d, bhat, x, o.use_x0 ? 1 : 0,
-                           reinterpret_cast<float *>(base + L.vec[0][0]), cx.partials);
+                           reinterpret_cast<float *>(base + L.vec[0][0]), cx.partials, &cx.sync->count, cx.ctl,
+                           srep);
     else
         hipLaunchKernelGGL(k_setup<double>, sgrid, sblock, 0, cx.stream, src, src_is_rhs, op->w,
                            op->geo, d, bhat, x, o.use_x0 ? 1 : 0,
-                           reinterpret_cast<double *>(base + L.vec[0][0]), cx.partials);
+                           reinterpret_cast<double *>(base + L.vec[0][0]), cx.partials, &cx.sync->count, cx.ctl,
+                           srep);
     LAUNCHCHK();
     double sums0[3] = {0.0, 0.0, 0.0};
-    st = reduce_n(cx, 3, sums0);
+    st = get_sums(cx, srep, 3, sums0);
     if (st != MAS_OK) return st;
     const double b2 = sums0[0];
     // r^0 into r (the first residual vector): already there from x^ = 0,
@@ -1358,9 +1421,7 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
                 status = MAS_EBREAKDOWN;
                 break;
             }
-            Ctl h;
-            st = read_ctl(cx, &h);
-            if (st != MAS_OK) return st;
+            const Ctl &h = pr.ctl[0];
             info.rel_resid_recursive = std::sqrt(h.rw) / bnorm;
             hipLaunchKernelGGL(k_fold, sgrid, sblock, 0, cx.stream, dh, d, x);
             LAUNCHCHK();
@@ -1403,9 +1464,7 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
             if (st != MAS_OK) return st;
             timing_summary(cx, pr.last_iter[0], &info);
             info.iters = pr.last_iter[0];
-            Ctl h;
-            st = read_ctl(cx, &h);
-            if (st != MAS_OK) return st;
+            const Ctl &h = pr.ctl[0];
             info.rel_resid_recursive = std::sqrt(h.rw) / bnorm;
             st = residual<double>(cx, bhat, x, r, &rw2);
             if (st != MAS_OK) return st;
@@ -1453,9 +1512,7 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
             if (st != MAS_OK) return st;
             timing_summary(cx, pr.last_iter[0], &info);
             info.iters = pr.last_iter[0];
-            Ctl h;
-            st = read_ctl(cx, &h);
-            if (st != MAS_OK) return st;
+            const Ctl &h = pr.ctl[0];
             info.rel_resid_recursive = std::sqrt(h.rw) / bnorm;
             // true residual of x_k into the buffer the next iteration reads
             const int nxt = (pr.last_iter[0] + 1) & 1;
@@ -1529,9 +1586,7 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
                 status = MAS_EBREAKDOWN;
                 break;
             }
-            Ctl h;
-            st = read_ctl(cx, &h);
-            if (st != MAS_OK) return st;
+            const Ctl &h = pr.ctl[0];
             const int nxt = (pr.last_iter[0] + 1) & 1;
             if (reliable) {
                 // x^ += d^ + alpha_K p_K, then replace r by the double-precision
@@ -1603,6 +1658,10 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
     cx.launch = o.launch;
     const Dims d = s.dims();
     const dim3 sgrid = s.simple_grid(), sblock(kWave, kSimpleJ);
+    {
+        const int e = begin_call(cx);
+        if (e != MAS_OK) return e;
+    }
     const double *const c[3] = {op->c64[0], op->c64[1], op->c64[2]};
 
     RhsSet<double> v;
@@ -1623,11 +1682,13 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
         kernels[h] = 0;
         set_halo(v, base, L, h);
         // b^ = W^-1 V rhs, x^ = W x0 or 0, ||b||^2 (and r^0 = b^ from x^ = 0)
+        const Report srep = new_report(cx.box);
         hipLaunchKernelGGL(k_setup<double>, sgrid, sblock, 0, stream, rhs + h * n, 1, op->w, op->geo,
-                           d, bhat[h], v.x[h], o.use_x0 ? 1 : 0, v.r[h][0], cx.partials);
+                           d, bhat[h], v.x[h], o.use_x0 ? 1 : 0, v.r[h][0], cx.partials,
+                           &cx.sync->count, cx.ctl, srep);
         LAUNCHCHK();
         double sums0[3] = {0.0, 0.0, 0.0};
-        int st = reduce_n(cx, 3, sums0);
+        int st = get_sums(cx, srep, 3, sums0);
         if (st != MAS_OK) return st;
         const double b2 = sums0[0];
         bnorm[h] = std::sqrt(b2);
@@ -1696,9 +1757,7 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
                 if (!active[h]) continue;
                 last = std::max(last, pr.last_iter[h]);
                 info[h].iters += pr.last_iter[h] - iter0;
-                Ctl hc;
-                st = read_ctl(cx, &hc, h);
-                if (st != MAS_OK) return st;
+                const Ctl &hc = pr.ctl[h];
                 info[h].rel_resid_recursive = std::sqrt(hc.rw) / bnorm[h];
                 st = residual<double>(cx, bhat[h], v.x[h], pv.r[h], &rw2[h]);
                 if (st != MAS_OK) return st;
@@ -1748,9 +1807,7 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
             if (!v.active[h]) continue;
             kernels[h] += pr.last_iter[h] - iter0 + 1;
             info[h].iters = kernels[h] - 1;
-            Ctl hc;
-            st = read_ctl(cx, &hc, h);
-            if (st != MAS_OK) return st;
+            const Ctl &hc = pr.ctl[h];
             info[h].rel_resid_recursive = std::sqrt(hc.rw) / bnorm[h];
             // true residual of x_k into the buffer the next run starts from
             st = residual<double>(cx, bhat[h], v.x[h], v.r[h][(last + 1) & 1], &rw2[h]);
@@ -1828,6 +1885,10 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
     const bool pc2 = o.precond == MAS_PC2;
     const bool reliable = !pc2 && o.refine == MAS_REFINE_RELIABLE;
 
+    {
+        const int e = begin_call(cx);
+        if (e != MAS_OK) return e;
+    }
     RhsSet<float> v;
     v.n = NR;
     double *bhat[NR], *xh[NR];
@@ -1849,11 +1910,13 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
         set_halo(v, base, L, h);
         used[h] = 0;
         // b^, x^ (and r^0 = b^ from x^ = 0), ||b||^2
+        const Report srep = new_report(cx.box);
         hipLaunchKernelGGL(k_setup<float>, sgrid, sblock, 0, stream, rhs + h * n, 1, op->w, op->geo,
-                           d, bhat[h], xh[h], o.use_x0 ? 1 : 0, v.r[h][0], cx.partials);
+                           d, bhat[h], xh[h], o.use_x0 ? 1 : 0, v.r[h][0], cx.partials,
+                           &cx.sync->count, cx.ctl, srep);
         LAUNCHCHK();
         double sums0[3] = {0.0, 0.0, 0.0};
-        int st = reduce_n(cx, 3, sums0);
+        int st = get_sums(cx, srep, 3, sums0);
         if (st != MAS_OK) return st;
         bnorm[h] = std::sqrt(sums0[0]);
         info[h].bnorm = bnorm[h];
@@ -1961,9 +2024,7 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
                 info[h].status = MAS_EBREAKDOWN;
                 continue;
             }
-            Ctl hc;
-            st = read_ctl(cx, &hc, h);
-            if (st != MAS_OK) return st;
+            const Ctl &hc = pr.ctl[h];
             if (pc2) {
                 info[h].rel_resid_recursive = std::sqrt(hc.rw) / bnorm[h];
                 hipLaunchKernelGGL(k_fold, sgrid, sblock, 0, stream, dh[h], d, xh[h]);

@@ -244,8 +244,8 @@ __global__ __launch_bounds__(kWave) void k_pc2_factor(Pc2FacArgs a, TOUT *dout) 
 }
 
 // z = M^-1 r for NR right-hand sides, first applying r -= alpha q when
-// a.update; per-block partials (r, z) and ||W r||^2 of each (right-hand side
-// h's at partials + 2 h nblk).  A right-hand side whose control block is
+// a.update; per-block partials (r, z) and ||W r||^2 of each (values 2 h and
+// 2 h + 1 of [][nblk]).  A right-hand side whose control block is
 // stopped is left alone.
 // With L the strictly lower couplings and D = diag(d), M = (D - L) D^-1 (D - L^T),
 // the forward sweep gives y = (D - L)^-1 r and z = (D - L^T)^-1 D y, so
@@ -285,7 +285,8 @@ struct Pc2Args {
     const T *q[NR];
     double *partials;
     Ctl *ctl;               // [NR]
-    uint32_t *count;        // blocks that have finished (last_block)
+    BlockCount *count;
+    Report rep;
     Dims dm;
     int nbi, nbj, nbk;      // blocks per direction
     int update;             // 1: r -= alpha q first; 0: the solve of a run's initial residual
@@ -481,18 +482,26 @@ void k_pc2_solve(Pc2Args<T, NR> a) {
         if (threadIdx.x < 2) {
             double v = 0.0;
             for (int u = 0; u < ni; ++u) v += sRed[u][threadIdx.x];
-            st_agent(a.partials + (int64_t)2 * h * nblk + 2 * (int64_t)blk + threadIdx.x, v);
+            st_agent(a.partials + (int64_t)(2 * h + threadIdx.x) * nblk + blk, v);
         }
         if (h + 1 < NR) __syncthreads();
     }
-    // the finalize, by the block that finishes last
-    if (!last_block(a.count, (uint32_t)nblk)) return;
+    // the finalize, by the block that finishes last; thread c takes right-hand
+    // side c
+    if (!last_block(a.count, (uint32_t)nblk, blockIdx.x)) return;
+    __shared__ double sSum[kPc2I * 2 * NR];
+    double S[2 * NR];
+    sum_partials<kPc2Threads, 2 * NR>(a.partials, nblk, S, sSum);
+    const int c = threadIdx.x;
+    if (c < NR && a.ctl[c].flag == FLAG_RUN) {
+        double rz = S[0], rw = S[1];
 #pragma unroll
-    for (int h = 0; h < NR; ++h) {
-        if (!run[h]) continue;
-        double S[2];
-        sum_partials<kPc2Threads, 2>(a.partials + (int64_t)2 * h * nblk, nblk, 2, S, &sRed[0][0]);
-        if (threadIdx.x == 0) pc2_beta(a.ctl + h, S[0], S[1], !upd);
+        for (int h = 1; h < NR; ++h) {
+            rz = (c == h) ? S[2 * h] : rz;
+            rw = (c == h) ? S[2 * h + 1] : rw;
+        }
+        pc2_beta(a.ctl + c, rz, rw, !upd);
+        report_ctl(a.rep, c, a.ctl + c);
     }
 }
 
