@@ -259,7 +259,8 @@ typedef struct {
     int32_t sample_timing; /* nonzero: time the step and a sample of its stage
                               kernels with HIP events and wait for completion    (0) */
     int32_t single_stage_kernels; /* nonzero: one stage per kernel.  Zero: for even
-                              np, stages 2..s run two per kernel (the second
+                              np, and for odd np on grids of at least 2^19 cells,
+                              stages 2..s run two per kernel (the second
                               stage formed from the first on each tile plus a
                               two-cell overlap ring), equal bit for bit to one
                               stage per kernel                                   (0) */

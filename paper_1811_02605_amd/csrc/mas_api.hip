@@ -2351,6 +2351,39 @@ extern "C" int64_t mas_sts_workspace_bytes(const mas_op *op) {
     return sts_work_layout(op->s).total;
 }
 
+// r planes per chunk of a stage kernel with `tiles` tiles per plane.  A grid
+// that gives every CU several blocks in turn takes `big` planes (see the
+// kernels' launches).  A smaller one is bound by the chain of plane steps of
+// the blocks a CU runs in turn: as many rounds of at most `slots` co-resident
+// blocks per CU as the blocks need, each of t + `steps` plane steps (steps:
+// what a block spends before and after its planes, in plane steps); the t that
+// makes that shortest.  us per stage, two / one per launch, against 32- and
+// 16-plane chunks: 16 x 16 x 32 cells 3.8 / 4.0 (16.9 / 16.9), 32 x 32 x 64
+// 4.0 / 4.1 (31.1 / 18.2), 64 x 96 x 192 11.0 / 14.0 (32.4 / 23.4), 128 x 192 x
+// 384 49.9 / 71.7 (65.2 / 71.7).  steps 2 / 1 and 6 / 5: the same within 3%,
+// single stages up to 10% slower on the smallest grids.
+constexpr int kStsSlots = 4, kStsSteps = 3, kPairSlots = 1, kPairSteps = 4;
+static int sts_chunk(const Shape &s, int64_t tiles, int big, int most, int slots, int steps) {
+    const int cap = s.max_chunk();
+    big = std::min(big, cap);
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        return big;
+    const int64_t room = (int64_t)ncu * slots;
+    if (tiles * ((s.nr + big - 1) / big) >= 4 * room) return big;
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int t = 1; t <= std::min({most, cap, s.nr}); ++t) {
+        const int64_t rounds = (tiles * ((s.nr + t - 1) / t) + room - 1) / room;
+        if (rounds * (t + steps) < cost) {
+            cost = rounds * (t + steps);
+            best = t;
+        }
+    }
+    return best;
+}
+
 // One stage kernel: out = a X + b Z + g L0 + Y0 + m dtL(X).
 static int sts_launch(const mas_op *op, hipStream_t stream, const double *X, const double *Z,
                       const double *L0, const double *Y0, double *out, double a, double b,
@@ -2358,10 +2391,10 @@ static int sts_launch(const mas_op *op, hipStream_t stream, const double *X, con
     const Shape &s = op->s;
     const int v = (s.np % 2 == 0) ? 2 : 1;
     const int seg = (kWave / kStsRPW) * v;
-    const int ti = std::min(kStsTI, s.max_chunk());
-    const int64_t tiles_i = (s.nr + ti - 1) / ti;
     const int64_t tiles_k = (s.np + seg - 1) / seg;
     const int64_t tiles_j = (s.nt + kStsWPB * kStsRPW - 1) / (kStsWPB * kStsRPW);
+    const int ti = sts_chunk(s, tiles_k * tiles_j, kStsTI, kStsTI, kStsSlots, kStsSteps);
+    const int64_t tiles_i = (s.nr + ti - 1) / ti;
     const int64_t nblk = tiles_i * tiles_k * tiles_j;
     if (nblk > INT32_MAX) return fail(MAS_EINVAL, "grid too large for the stage kernel");
     StsArgs args{X, op->nu, Z, L0, Y0, out, a, b, g, m * op->dt, op->geo, s.dims(),
@@ -2390,9 +2423,12 @@ static int sts_launch(const mas_op *op, hipStream_t stream, const double *X, con
     return MAS_OK;
 }
 
-// The two-stage kernel keeps the lane's two cells adjacent across the
-// periodic seam only for even np; odd np runs one stage per launch.
-static bool sts_pairs_ok(const Shape &s) { return s.np % 2 == 0; }
+// Whether stages run two per kernel.  An odd np takes two accesses for a
+// lane's two cells, which pays where memory is the bound: 75 x 131 x 261 cells
+// 21.9 us a stage against 32.6 with one stage per launch; 45 x 65 x 129 cells
+// 6.8 against 6.7, 14 x 43 x 107 cells 4.5 against 4.1.
+static constexpr int64_t kPairOddCells = (int64_t)1 << 19;
+static bool sts_pairs_ok(const Shape &s) { return s.np % 2 == 0 || (s.n >= kPairOddCells && s.np >= 3); }
 
 // Stages j, j+1 in one kernel (k_sts_pair): outA = aA X + bA Z + gA L0 +
 // mA dtL(X), outB = aB outA + bB X + gB L0 + Y0 + mB dtL(outA).  L0 == nullptr
@@ -2404,25 +2440,33 @@ static int sts_pair_launch(const mas_op *op, hipStream_t stream, const double *X
     constexpr int RO = 2 * kPairNW - 4;
     // r chunks: at least kPairTI planes, and long enough that there are at
     // most 8 of them (whole r slabs per XCD, as for the iteration kernel)
-    const int ti = std::min(s.max_chunk(), MAS_PAIR_SLAB ? std::min(kPairMaxTI, std::max(kPairTI, (s.nr + 7) / 8))
-                                                         : kPairTI);
-    const int64_t tiles_i = (s.nr + ti - 1) / ti;
     const int64_t tiles_k = (s.np + kPairOut - 1) / kPairOut;
     const int64_t tiles_j = (s.nt + RO - 1) / RO;
+    const int ti = sts_chunk(s, tiles_k * tiles_j, std::min(kPairMaxTI, std::max(kPairTI, (s.nr + 7) / 8)),
+                             kPairMaxTI, kPairSlots, kPairSteps);
+    const int64_t tiles_i = (s.nr + ti - 1) / ti;
     const int64_t nblk = tiles_i * tiles_k * tiles_j;
     if (nblk > INT32_MAX) return fail(MAS_EINVAL, "grid too large for the stage kernel");
-    if (!sts_pairs_ok(s)) return fail(MAS_EINVAL, "internal: two-stage kernel needs an even np");
+    if (!sts_pairs_ok(s)) return fail(MAS_EINVAL, "internal: one stage per kernel on this grid");
     StsPairArgs args{X, op->nu, Z, L0, Y0, outA, outB, aA, bA, gA, mA * op->dt, aB, bB, gB, mB * op->dt,
                      op->geo, s.dims(), (int)tiles_i, (int)tiles_k, (int)tiles_j, ti, (int)nblk};
     const int in = (Z ? kPairZ : 0) | (L0 ? kPairL : 0) | (Y0 ? kPairY : 0);
     const dim3 grid((unsigned)nblk), block(kWave * kPairNW);
-    switch (in) {
-        case 0: hipLaunchKernelGGL((k_sts_pair<kPairNW, 0>), grid, block, 0, stream, args); break;
-        case kPairY: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairY>), grid, block, 0, stream, args); break;
-        case kPairZ | kPairL: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairZ | kPairL>), grid, block, 0, stream, args); break;
-        case kPairZ | kPairL | kPairY: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairZ | kPairL | kPairY>), grid, block, 0, stream, args); break;
-        default: return fail(MAS_EINVAL, "internal: unsupported stage-pair inputs %d", in);
-    }
+    auto go = [&](auto odd) {
+        constexpr bool O = decltype(odd)::value;
+        switch (in) {
+            case 0: hipLaunchKernelGGL((k_sts_pair<kPairNW, 0, O>), grid, block, 0, stream, args); break;
+            case kPairY: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairY, O>), grid, block, 0, stream, args); break;
+            case kPairZ | kPairL: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairZ | kPairL, O>), grid, block, 0, stream, args); break;
+            default: hipLaunchKernelGGL((k_sts_pair<kPairNW, kPairZ | kPairL | kPairY, O>), grid, block, 0, stream, args); break;
+        }
+    };
+    if (in != 0 && in != kPairY && in != (kPairZ | kPairL) && in != (kPairZ | kPairL | kPairY))
+        return fail(MAS_EINVAL, "internal: unsupported stage-pair inputs %d", in);
+    if (s.np % 2 == 0)
+        go(std::false_type{});
+    else
+        go(std::true_type{});
     LAUNCHCHK();
     return MAS_OK;
 }

@@ -74,7 +74,8 @@ struct StsPlaneRaw {
 };
 
 __device__ inline StsPlaneRaw sts_plane_raw(const Geo &g, int m) {
-    return StsPlaneRaw{g.gq[m], g.gr[m], (m > 0) ? g.gr[m - 1] : 0.0, g.vr[m], m};
+    return StsPlaneRaw{ld_table(g.gq, m), ld_table(g.gr, m), (m > 0) ? ld_table(g.gr, m - 1) : 0.0,
+                       ld_table(g.vr, m), m};
 }
 
 __device__ inline StsPlane sts_plane(const Geo &g, const StsPlaneRaw &t, int nr, double vt, double mdt) {
@@ -325,7 +326,7 @@ struct StsPairArgs {
 #define MAS_PAIR_WPE 2
 #endif
 
-template <int NW, int IN>
+template <int NW, int IN, bool ODD>
 __global__ __launch_bounds__(kWave *NW) __attribute__((amdgpu_waves_per_eu(MAS_PAIR_WPE, 8)))
 void k_sts_pair(StsPairArgs a) {
     constexpr int R = 2 * NW;  // tile rows
@@ -354,15 +355,30 @@ void k_sts_pair(StsPairArgs a) {
     const int ru = rho > 0 ? rho - 1 : rho, rd = rho < R - 1 ? rho + 1 : rho;
     const int j = jt * RO - 2 + rho;
     const int k0 = kt * kPairOut;
-    const int nout = min(kPairOut, np - k0);  // even: np is even
+    const int nout = min(kPairOut, np - k0);  // even if np is
     const bool rowin = j >= 0 && j < nt;
-    // the lane's two cells k0 - 2 + c, +1 (periodic; np even keeps them adjacent)
-    const bool ld = rowin && c <= nout + 2;
-    int k = k0 - 2 + c;
-    if (k < 0) k += np;
-    else if (k >= np) k -= np;
-    const int64_t col = ld ? (int64_t)j * np + k : 0;
-    const bool own = rowin && rho >= 2 && rho < R - 2 && c >= 2 && c < nout + 2;
+    // the lane's two cells k0 - 2 + c, +1 (periodic).  An even np keeps them
+    // adjacent in memory and both in or out: one 16-byte access at the first
+    // (E = 1); an odd one (at least 3) takes two 8-byte accesses.
+    constexpr int E = ODD ? 2 : 1;
+    struct Cell {
+        bool ld;    // in the tile and the grid
+        bool zl;    // reads Z and L0: they enter stage A only, whose values on
+                    // the outermost tile rows are never used
+        bool own;   // kept
+        int64_t col;
+    } cell[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int cc = c + e;
+        int k = k0 - 2 + cc;
+        if (k < 0) k += np;
+        else if (k >= np) k -= np;
+        cell[e].ld = rowin && cc < nout + 4;
+        cell[e].zl = cell[e].ld && rho >= 1 && rho < R - 1;
+        cell[e].own = rowin && rho >= 2 && rho < R - 2 && cc >= 2 && cc < nout + 2;
+        cell[e].col = cell[e].ld ? (int64_t)j * np + k : 0;
+    }
 
     const int jj = rowin ? j : 0;
     const double vt = a.geo.vt[jj];
@@ -380,34 +396,44 @@ void k_sts_pair(StsPairArgs a) {
     const auto RX = win_rsrc(a.X, win), RN = win_rsrc(a.nu, win), RZ = win_rsrc(a.Z, win, HZ),
                RL = win_rsrc(a.L0, win, HL), RY = win_rsrc(a.Y0, win, HY),
                RA = win_rsrc(a.outA, win, !HY), RB = win_rsrc(a.outB, win);
-    auto ldoff = [&](int m) -> uint32_t {
-        return (ld && m >= 0 && m < nr) ? (uint32_t)((int64_t)(m - win.lo) * plane + col) * ES : kOOB;
+    struct Off {
+        uint32_t o[E];
     };
-    // Z and L0 enter stage A only, whose values on the outermost tile rows
-    // are never used: those rows do not load them
-    const bool ldzl = ld && rho >= 1 && rho < R - 1;
-    auto zloff = [&](int m) -> uint32_t {
-        return (ldzl && m >= 0 && m < nr) ? (uint32_t)((int64_t)(m - win.lo) * plane + col) * ES : kOOB;
+    auto off_if = [&](int m, auto on) {
+        Off f;
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            f.o[e] = on(cell[e]) ? (uint32_t)((int64_t)(m - win.lo) * plane + cell[e].col) * ES : kOOB;
+        return f;
     };
-    auto ownoff = [&](int m) -> uint32_t {
-        return (own && m >= i0 && m < i1) ? (uint32_t)((int64_t)(m - win.lo) * plane + col) * ES : kOOB;
+    auto ldoff = [&](int m) { return off_if(m, [&](const Cell &q) { return q.ld && m >= 0 && m < nr; }); };
+    auto zloff = [&](int m) { return off_if(m, [&](const Cell &q) { return q.zl && m >= 0 && m < nr; }); };
+    auto ownoff = [&](int m) { return off_if(m, [&](const Cell &q) { return q.own && m >= i0 && m < i1; }); };
+    auto ld2 = [&](auto aux, __amdgpu_buffer_rsrc_t r, const Off &f) -> VD {
+        constexpr int AUX = decltype(aux)::value;
+        if constexpr (ODD) return VD{{bld<double, 1, AUX>(r, f.o[0]).v[0], bld<double, 1, AUX>(r, f.o[E - 1]).v[0]}};
+        else return bld<double, 2, AUX>(r, f.o[0]);
     };
+    auto st2 = [&](__amdgpu_buffer_rsrc_t r, const Off &f, const VD &v) {
+        if constexpr (ODD) {
+            bst<double, 1, MAS_STS_AUX_ST>(r, f.o[0], VecT<double, 1>{{v.v[0]}});
+            bst<double, 1, MAS_STS_AUX_ST>(r, f.o[E - 1], VecT<double, 1>{{v.v[1]}});
+        } else {
+            bst<double, 2, MAS_STS_AUX_ST>(r, f.o[0], v);
+        }
+    };
+    constexpr std::integral_constant<int, MAS_STS_AUX_XN> kXN{};
+    constexpr std::integral_constant<int, MAS_STS_AUX_ZL> kZL{};
+    constexpr std::integral_constant<int, 0> kPlain{};
     auto lds2 = [&](const double *row) -> VD { return VD{{row[c], row[c + 1]}}; };
 
     // The chunk's plane-table entries, planes i0-2 .. i1+1 (clamped into the
-    // grid; A is zero outside it), copied to LDS once: read there each step,
+    // grid; A is zero outside it), copied to LDS once (below, behind the first
+    // planes' loads): read there each step,
     // they put no wait on the vector-memory counter that the loads queued for
     // the next step also count on.
     __shared__ double sG[kPairMaxTI + 4][4];
     auto clampm = [&](int m) { return min(max(m, 0), nr - 1); };
-    for (int t = threadIdx.x; t < i1 - i0 + 4; t += kWave * NW) {
-        const StsPlaneRaw r = sts_plane_raw(a.geo, clampm(i0 - 2 + t));
-        sG[t][0] = r.gq;
-        sG[t][1] = r.gr;
-        sG[t][2] = r.grm;
-        sG[t][3] = r.vr;
-    }
-    __syncthreads();
     auto table = [&](int m) {
         const int t = m - (i0 - 2);
         return StsPlaneRaw{sG[t][0], sG[t][1], sG[t][2], sG[t][3], clampm(m)};
@@ -420,27 +446,35 @@ void k_sts_pair(StsPairArgs a) {
     // register queues: X and nu at planes m - dir (b), m (c), m + dir (a);
     // Z and L0 at m (c); L0 at m - dir (b).  Each step loads X and nu of plane
     // m + 2 dir and Z and L0 of plane m + dir for the next step.
-    VD Xb = bld<double, 2, MAS_STS_AUX_XN>(RX, ldoff(first - dir));
-    VD Nb = bld<double, 2, MAS_STS_AUX_XN>(RN, ldoff(first - dir));
-    VD Xc = bld<double, 2, MAS_STS_AUX_XN>(RX, ldoff(first));
-    VD Nc = bld<double, 2, MAS_STS_AUX_XN>(RN, ldoff(first));
-    VD Xa = bld<double, 2, MAS_STS_AUX_XN>(RX, ldoff(first + dir));
-    VD Na = bld<double, 2, MAS_STS_AUX_XN>(RN, ldoff(first + dir));
+    VD Xb = ld2(kXN, RX, ldoff(first - dir));
+    VD Nb = ld2(kXN, RN, ldoff(first - dir));
+    VD Xc = ld2(kXN, RX, ldoff(first));
+    VD Nc = ld2(kXN, RN, ldoff(first));
+    VD Xa = ld2(kXN, RX, ldoff(first + dir));
+    VD Na = ld2(kXN, RN, ldoff(first + dir));
     VD Zc{}, Lc{}, Lb_{};
-    if constexpr (HZ) Zc = bld<double, 2>(RZ, zloff(first));
-    if constexpr (HL) Lc = bld<double, 2>(RL, zloff(first));
+    if constexpr (HZ) Zc = ld2(kPlain, RZ, zloff(first));
+    if constexpr (HL) Lc = ld2(kPlain, RL, zloff(first));
 
+    for (int t = threadIdx.x; t < i1 - i0 + 4; t += kWave * NW) {
+        const StsPlaneRaw r = sts_plane_raw(a.geo, clampm(i0 - 2 + t));
+        sG[t][0] = r.gq;
+        sG[t][1] = r.gr;
+        sG[t][2] = r.grm;
+        sG[t][3] = r.vr;
+    }
+    __syncthreads();
     for (int s = 0; s < nsteps; ++s) {
         const int m = first + s * dir;
         const int mb = m - dir;  // plane of stage B
         const int q0 = s & 3, q1 = (s - 1) & 3, q2 = (s - 2) & 3, x0 = s & 1;
         // ---- loads for the next step (and Y0 of this step's B)
-        const VD Xn = bld<double, 2, MAS_STS_AUX_XN>(RX, ldoff(m + 2 * dir));
-        const VD Nn = bld<double, 2, MAS_STS_AUX_XN>(RN, ldoff(m + 2 * dir));
+        const VD Xn = ld2(kXN, RX, ldoff(m + 2 * dir));
+        const VD Nn = ld2(kXN, RN, ldoff(m + 2 * dir));
         VD Zn{}, Ln{}, Yo{};
-        if constexpr (HZ) Zn = bld<double, 2>(RZ, zloff(m + dir));
-        if constexpr (HL) Ln = bld<double, 2>(RL, zloff(m + dir));
-        if constexpr (HY) Yo = bld<double, 2, MAS_STS_AUX_ZL>(RY, s >= 2 ? ownoff(mb) : kOOB);
+        if constexpr (HZ) Zn = ld2(kPlain, RZ, zloff(m + dir));
+        if constexpr (HL) Ln = ld2(kPlain, RL, zloff(m + dir));
+        if constexpr (HY) Yo = ld2(kZL, RY, off_if(mb, [&](const Cell &q) { return s >= 2 && q.own && mb >= i0 && mb < i1; }));
 
         // ---- X and nu of plane m to LDS; A of plane mb went there last step
         sX[x0][rho][c] = Xc.v[0];
@@ -498,11 +532,11 @@ void k_sts_pair(StsPairArgs a) {
                 const double lv = HL ? Lb_.v[e] : Xb.v[e];
                 o.v[e] = sts_combine(a.aB, yc, a.bB, Xb.v[e], a.gB, lv, Yo.v[e], pf.scale, f);
             }
-            bst<double, 2, MAS_STS_AUX_ST>(RB, ownoff(mb), o);
+            st2(RB, ownoff(mb), o);
         }
         sY[q0][rho][c] = Yc.v[0];
         sY[q0][rho][c + 1] = Yc.v[1];
-        if constexpr (!HY) bst<double, 2, MAS_STS_AUX_ST>(RA, ownoff(m), Yc);
+        if constexpr (!HY) st2(RA, ownoff(m), Yc);
 
         Nb = Nc;
         Xb = Xc;

@@ -198,3 +198,17 @@ def test_timing_info_and_argument_errors(pairs):
     st = lib.mas_sts_step(op.handle, u0.data_ptr(), out.data_ptr(), None, out.data_ptr(), need - 8,
                           None, None)
     assert st == abi.MAS_ENOMEM
+
+
+# odd np at which stages run in pairs (at least 2^19 cells): last tile of 55 and
+# of 1 column, ragged theta tiles, one and several r chunks
+@pytest.mark.parametrize("shape", [(41, 113, 115), (45, 65, 181), (3, 420, 419)])
+@pytest.mark.parametrize("stages", [3, 4, 8])
+def test_odd_width_pairs_equal_single_stage_kernels(shape, stages):
+    p = problem(shape, (1, 0))
+    _, op = gpu_operator(p)
+    u0 = to_dev(np.random.default_rng(31).standard_normal(p.shape))
+    a, ia = op.sts_step(u0, stages=stages)
+    b, ib = op.sts_step(u0, stages=stages, stage_pairs=False)
+    assert ia["stages_per_kernel"] == 2 and ib["stages_per_kernel"] == 1
+    assert torch.equal(a, b)
