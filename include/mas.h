@@ -131,9 +131,10 @@ typedef struct {
  *     Needs PC1, no sample_timing and a grid whose iteration kernel fits on
  *     the GPU at once (small grids, where launches and latency, not
  *     bandwidth, set the time); MAS_EINVAL otherwise.
- *     With chunk_planes = 0 its r chunks are long enough for about 64
- *     blocks; with the same chunk_planes both modes give the same results
- *     bit for bit (other chunks sum the partial dot products in another
+ *     With chunk_planes = 0 a grid of at most 2^17 cells runs with a cell
+ *     per thread, a larger one in r chunks long enough for about 64
+ *     blocks; with the same chunk_planes > 0 both modes give the same results
+ *     bit for bit (otherwise the partial dot products are summed in another
  *     order).  Its blocks wait for each other at every iteration, at most
  *     2 s: if kernels of other streams keep part of its blocks from
  *     starting for longer, the call returns MAS_EHIP instead of hanging.

@@ -104,19 +104,41 @@ __device__ inline T ld_table(const T *p, int64_t i) {
 }
 
 // ---------------------------------------------------------------- reductions
+// v from the lane a DPP move names, 0 where none is.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_or_zero(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+// Sum over the wave, for every lane: row shifts by 1, 2, 4 and 8, the row sums
+// broadcast to the next rows, lane 63's total to all.  The moves stay in the
+// vector ALU; by lane shuffles through the LDS crossbar a solve on 64 x 96 x 192
+// cells took 4.19 instead of 4.10 ms, four right-hand sides on 32 x 64 x 64 in
+// one launch 2.26 instead of 1.92.
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, kWave - 1);
+    const uint64_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), kWave - 1);
+    return __builtin_bit_cast(double, lo | (hi << 32));
 }
 
 // Data that blocks of one launch pass to each other: stores and loads at agent
 // scope go past the L2 of the XCD (which is not coherent with the other seven)
 // with no write-back or invalidation of anything else.
-__device__ inline void st_agent(double *p, double v) {
+template <typename T>
+__device__ inline void st_agent(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline double ld_agent(const double *p) {
+template <typename T>
+__device__ inline T ld_agent(const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -147,6 +169,9 @@ __device__ inline void block_sum_store(double (&v)[NV], double *out, int64_t nbl
     }
 }
 
+// Wait until this wave's stores have been acknowledged.
+__device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Counters of the blocks of a launch that have finished: kCountGroups groups of
 // blocks count in lines of their own and the last block of each group counts
 // in the first line.  Additions to one line take turns: with one counter for
@@ -168,7 +193,7 @@ __device__ inline bool last_block(BlockCount *count, uint32_t nblk, uint32_t blk
     __shared__ int last;
     const int tid = threadIdx.x + threadIdx.y * blockDim.x;
     if (tid < kWave) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wait_stores();
         if (tid == 0) {
             auto add = [](uint32_t *c, uint32_t of) {
                 const bool full = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == of - 1;
@@ -1184,6 +1209,7 @@ struct PersistArgs {
 // otherwise leave the others waiting for good).
 __device__ inline bool grid_barrier(PersistSync *sync, uint32_t target, uint64_t wait_ticks) {
     __shared__ int ok;
+    wait_stores();  // every wave's own, before one thread releases for all
     __syncthreads();
     if (threadIdx.x == 0) {
         __hip_atomic_fetch_add(&sync->bar, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1292,6 +1318,220 @@ __global__ __launch_bounds__(256) void k_x_catchup(CatchupArgs<T> a) {
     const T *p = a.p[c][last & 1];
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < a.n; i += (int64_t)gridDim.x * 256)
         x[i] = x[i] + al * p[i];
+}
+
+// ---------------------------------------------------------------- persistent run, one cell per thread
+// The same run for grids of at most kSmallCells cells, with a cell per thread:
+// r, p, q, x, w and the couplings stay in its registers for the whole run, and
+// an iteration is one exchange between the blocks instead of passes over
+// memory.  What bounds such a grid is that exchange (3-5 us), so it is made of
+// as few dependent trips to the last-level cache as the recurrences allow:
+//   - every cell publishes r, p and q at agent scope; a neighbour's p_k is
+//     formed from them as everywhere (18 loads in one batch, whatever the
+//     block boundaries are);
+//   - once its stores are acknowledged, a block publishes its five sums as
+//     tagged words, the iteration's number beside each half of a double, so
+//     that a reader sees from the word itself that it is this iteration's;
+//   - every block reads all blocks' words until the tags match: that is the
+//     barrier and the reduction at once (no counter, no second read).
+// Each block sums in the same order and finalizes its own control block, so all
+// take the same decisions.  Slots and vectors alternate by parity: a block
+// writes a slot again only after every block has published the iteration
+// between, and so has read it.  The slots are cleared, behind one barrier with
+// a counter, before the first iteration.  Waits are bounded as in grid_barrier.
+// 32 x 32 x 64 cells: 6.0 us an iteration, 9.6 with tiles and their vectors in
+// memory (k_pcg_persist); 16 x 16 x 32 cells 4.0 and 7.6.
+constexpr int kSmallThreads = 512;  // 1024: 2-20% slower
+constexpr int64_t kSmallCells = (int64_t)1 << 17;
+constexpr int kSmallBlocks = (int)(kSmallCells / kSmallThreads);  // one thread polls each block
+
+template <typename T, int NR>
+struct SmallArgs {
+    T *r[NR][2], *p[NR][2], *q[NR][2], *x[NR];  // by parity: iteration k reads index k & 1
+    const T *cr, *ct, *cp;
+    const double *w;
+    uint64_t *slots;  // by parity, [NR * kNV * 2][nblk] each
+    Ctl *ctl;         // [NR] (k_run_init has set them)
+    PersistSync *sync;
+    Report rep;
+    Dims d;
+    int nblk, iter0;
+    int keep_p[NR];   // the first iteration continues the direction in p[c][iter0 & 1]
+    uint64_t wait_ticks;
+};
+
+template <typename T, int NR>
+__global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a) {
+    constexpr int NV = NR * kNV, NW = kSmallThreads / kWave;
+    __shared__ double sWave[NW][NV], sAll[kSmallBlocks / kWave][NV];
+    __shared__ Ctl sCtl[NR];
+    __shared__ int gave_up;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int nblk = a.nblk, blk = blockIdx.x;
+    const int np = a.d.np, nt = a.d.nt, plane = (int)a.d.plane, n = (int)a.d.n;
+    const int c = blk * kSmallThreads + tid;
+    const bool in = c < n;
+    for (int t = tid; t < 2 * 2 * NV; t += kSmallThreads) st_agent(a.slots + (int64_t)t * nblk + blk, (uint64_t)0);
+    if (tid < NR) sCtl[tid] = a.ctl[tid];
+    if (tid == 0) gave_up = 0;
+    // neighbours in the order -r, +r, -theta, +theta, -phi, +phi; one that is
+    // not there is the cell itself with no coupling
+    const int cc = in ? c : 0;
+    const int i = cc / plane, j = (cc % plane) / np, k_phi = cc % np;
+    const bool has[4] = {in && i > 0, in && i < a.d.nr - 1, in && j > 0, in && j < nt - 1};
+    const int nb[6] = {has[0] ? cc - plane : cc, has[1] ? cc + plane : cc, has[2] ? cc - np : cc,
+                       has[3] ? cc + np : cc, cc + (k_phi == 0 ? np - 1 : -1),
+                       cc + (k_phi == np - 1 ? 1 - np : 1)};
+    const T cf[6] = {has[0] ? a.cr[nb[0]] : T(0), has[1] ? a.cr[cc] : T(0), has[2] ? a.ct[nb[2]] : T(0),
+                     has[3] ? a.ct[cc] : T(0), in ? a.cp[nb[4]] : T(0), in ? a.cp[cc] : T(0)};
+    const double w = in ? a.w[cc] : 0.0;
+    T r[NR], p[NR], q[NR], x[NR];
+    {
+        const int cur = a.iter0 & 1;
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+            r[h] = in ? a.r[h][cur][cc] : T(0);
+            p[h] = a.keep_p[h] ? (in ? a.p[h][cur][cc] : T(0)) : r[h];
+            q[h] = r[h];  // alpha = 0
+            x[h] = in ? a.x[h][cc] : T(0);
+        }
+    }
+    if (!grid_barrier(a.sync, (uint32_t)nblk, a.wait_ticks)) {
+        if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
+        if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    Ctl lc = sCtl[0];  // NR = 1: every thread keeps its own copy
+    auto ctl_of = [&](int h) -> Ctl & {
+        if constexpr (NR == 1) return lc;
+        else return sCtl[h];
+    };
+    for (int k = a.iter0;; ++k) {
+        const int cur = k & 1, nxt = cur ^ 1, s = k - a.iter0;
+        double acc[NV];
+#pragma unroll
+        for (int t = 0; t < NV; ++t) acc[t] = 0.0;
+#pragma unroll
+        for (int h = 0; h < NR; ++h) {
+            const Ctl &ct = ctl_of(h);
+            if (ct.flag != FLAG_RUN) continue;  // uniform
+            const T alpha = (T)ct.alpha, beta = (T)ct.beta;
+            const T *R = a.r[h][cur], *Q = s == 0 ? R : a.q[h][cur],
+                    *P = (s == 0 && !a.keep_p[h]) ? R : a.p[h][cur];
+            T pn[6];
+            if (in) {
+                T rv[6], qv[6], pv[6];
+#pragma unroll
+                for (int t = 0; t < 6; ++t) {
+                    rv[t] = ld_agent(R + nb[t]);
+                    qv[t] = ld_agent(Q + nb[t]);
+                    pv[t] = ld_agent(P + nb[t]);
+                }
+#pragma unroll
+                for (int t = 0; t < 6; ++t) pn[t] = (rv[t] - alpha * qv[t]) + beta * pv[t];
+                x[h] = x[h] + alpha * p[h];
+                r[h] = r[h] - alpha * q[h];
+                p[h] = r[h] + beta * p[h];
+                const T S = cf[3] * pn[3] + cf[2] * pn[2] + cf[5] * pn[5] + cf[4] * pn[4] + cf[0] * pn[0];
+                q[h] = p[h] - (S + cf[1] * pn[1]);
+                st_agent(a.r[h][nxt] + cc, r[h]);
+                st_agent(a.p[h][nxt] + cc, p[h]);
+                st_agent(a.q[h][nxt] + cc, q[h]);
+                const double pd = (double)p[h], qd = (double)q[h], rd = (double)r[h], t = w * rd;
+                acc[h * kNV + 0] = pd * qd;
+                acc[h * kNV + 1] = rd * qd;
+                acc[h * kNV + 2] = qd * qd;
+                acc[h * kNV + 3] = rd * rd;
+                acc[h * kNV + 4] = t * t;
+            }
+        }
+        // the block's sums, as words tagged with the iteration's number
+#pragma unroll
+        for (int t = 0; t < NV; ++t) acc[t] = wave_sum(acc[t]);
+        if (lane == 0) {
+#pragma unroll
+            for (int t = 0; t < NV; ++t) sWave[wv][t] = acc[t];
+        }
+        wait_stores();
+        __syncthreads();
+        const uint32_t tag = (uint32_t)s + 1u;
+        uint64_t *slots = a.slots + (int64_t)cur * (2 * NV) * nblk;
+        if (tid < NV) {
+            double v = 0.0;
+            for (int u = 0; u < NW; ++u) v += sWave[u][tid];
+            const uint64_t b = __builtin_bit_cast(uint64_t, v), hi = (uint64_t)tag << 32;
+            st_agent(slots + (int64_t)(2 * tid) * nblk + blk, hi | (uint32_t)b);
+            st_agent(slots + (int64_t)(2 * tid + 1) * nblk + blk, hi | (b >> 32));
+        }
+        // every block's
+        if (wv < kSmallBlocks / kWave) {
+            double v[NV];
+#pragma unroll
+            for (int t = 0; t < NV; ++t) v[t] = 0.0;
+            if (tid < nblk) {
+                const uint64_t t0 = wall_clock64();
+                for (;;) {
+                    uint64_t g[2 * NV];
+#pragma unroll
+                    for (int t = 0; t < 2 * NV; ++t) g[t] = ld_agent(slots + (int64_t)t * nblk + tid);
+                    bool all = true;
+#pragma unroll
+                    for (int t = 0; t < 2 * NV; ++t) all = all && (uint32_t)(g[t] >> 32) == tag;
+                    if (all) {
+#pragma unroll
+                        for (int t = 0; t < NV; ++t)
+                            v[t] = __builtin_bit_cast(double, (g[2 * t] & 0xffffffffu) | (g[2 * t + 1] << 32));
+                        break;
+                    }
+                    if (wall_clock64() - t0 > a.wait_ticks) {
+                        gave_up = 1;
+                        break;
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
+            if (lane == 0) {
+#pragma unroll
+                for (int t = 0; t < NV; ++t) sAll[wv][t] = v[t];
+            }
+        }
+        __syncthreads();
+        if (gave_up) {
+            if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
+            if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        auto finalize = [&](Ctl &ct, int h) {
+            double S[kNV];
+#pragma unroll
+            for (int t = 0; t < kNV; ++t) {
+                S[t] = 0.0;
+#pragma unroll
+                for (int u = 0; u < kSmallBlocks / kWave; ++u) S[t] += sAll[u][h * kNV + t];
+            }
+            pcg_finalize(&ct, S);
+            if (blk == 0 && tid == h && ct.flag != FLAG_RUN) {
+                a.ctl[h] = ct;
+                report_ctl(a.rep, h, &ct);
+            }
+        };
+        bool any = false;
+        if constexpr (NR == 1) {
+            finalize(lc, 0);
+            any = lc.flag == FLAG_RUN;
+        } else {
+            if (tid < NR && sCtl[tid].flag == FLAG_RUN) finalize(sCtl[tid], tid);
+            __syncthreads();
+#pragma unroll
+            for (int h = 0; h < NR; ++h) any = any || sCtl[h].flag == FLAG_RUN;
+        }
+        if (!any) break;
+    }
+    if (in) {
+#pragma unroll
+        for (int h = 0; h < NR; ++h) a.x[h][cc] = x[h];
+    }
 }
 
 // Reset the control blocks and the counters for a new PCG run of n right-hand

@@ -491,6 +491,8 @@ extern "C" int mas_op_export(const mas_op *op, double *cr, double *ct, double *c
 }
 
 // ------------------------------------------------------------------ workspace
+static int64_t small_blocks(const Shape &s) { return (s.n + kSmallThreads - 1) / kSmallThreads; }
+
 struct WorkLayout {
     int64_t ctl, sync, partials, bhat[kMaxRhs], vec[kMaxRhs][6], halo[kMaxRhs][2], dh[kMaxRhs], total;
     int64_t halo_bytes;  // one record buffer (0: records not used)
@@ -506,7 +508,10 @@ static WorkLayout work_layout(const Shape &s, int precision, int nrhs = 1) {
     // the iteration kernel writes nrhs * kNV partials per block (most blocks
     // with V = 1), the simple-tile kernels up to kSimpleNV
     // (a persistent run keeps two sets, by parity)
-    const int64_t nparts = std::max(s.nblk_iter_max() * kNV * nrhs * 2, s.nblk_simple() * kSimpleNV);
+    const int64_t nparts =
+        std::max({s.nblk_iter_max() * kNV * nrhs * 2, s.nblk_simple() * kSimpleNV,
+                  // the tagged words of a persistent run with a cell per thread
+                  s.n <= kSmallCells ? small_blocks(s) * kNV * nrhs * 4 : (int64_t)0});
     L.ctl = take(sizeof(Ctl) * nrhs);
     L.sync = take(sizeof(PersistSync));
     L.partials = take(8 * nparts);
@@ -868,7 +873,8 @@ static const void *persist_kernel(int V) {
 }
 
 // Whether a PC1 run of NR right-hand sides goes into one persistent launch
-// (1) or a launch per iteration (0); MAS_EINVAL when the persistent launch
+// (1: tiles of r chunks; 2: a cell per thread, when no chunk length is asked
+// for and the grid is small enough) or a launch per iteration (0); MAS_EINVAL when the persistent launch
 // was asked for and is not possible.
 template <typename T, int NR>
 static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
@@ -889,6 +895,11 @@ static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
     HIPCHK(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
     if (!coop) return no("the device has no cooperative launch");
     HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    if (cx.chunk == 0 && s.n <= kSmallCells) {
+        HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&k_pcg_small<T, NR>),
+                                                            kSmallThreads, 0));
+        if ((int64_t)per_cu * ncu >= small_blocks(s)) return 2;
+    }
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_kernel<T, NR>(V), kWave * kTJ, 0));
     if ((int64_t)per_cu * ncu < nblk) return no("the iteration kernel's blocks do not fit on the GPU at once");
     return 1;
@@ -922,7 +933,7 @@ static int persist_gave_up() {
 // results as run_pcg's launches per iteration, bit for bit.
 template <typename T, int NR>
 static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, int iter0,
-                           int check_every, PcgResult *res) {
+                           int check_every, bool cell_per_thread, PcgResult *res) {
     const mas_op *op = cx.op;
     const Shape &s = op->s;
     hipStream_t st = cx.stream;
@@ -932,7 +943,38 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     LAUNCHCHK();
     RunWatch watch(cx, NR, v.active, iter0, 1);
     cx.launched = MAS_LAUNCH_PERSISTENT;
-    if (work) {
+    int dev = 0, khz = 0;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+    const uint64_t ticks = (uint64_t)((double)khz * 1000.0 * kPersistWaitSec);
+    if (work && cell_per_thread) {
+        SmallArgs<T, NR> sa{};
+        for (int h = 0; h < NR; ++h) {
+            for (int t = 0; t < 2; ++t) {
+                sa.r[h][t] = v.r[h][t];
+                sa.p[h][t] = v.p[h][t];
+                sa.q[h][t] = v.q[h][t];
+            }
+            sa.x[h] = v.x[h];
+            sa.keep_p[h] = v.keep_p[h] ? 1 : 0;
+        }
+        sa.cr = c[0];
+        sa.ct = c[1];
+        sa.cp = c[2];
+        sa.w = op->w;
+        sa.slots = reinterpret_cast<uint64_t *>(cx.partials);
+        sa.ctl = cx.ctl;
+        sa.sync = cx.sync;
+        sa.rep = watch.rep;
+        sa.d = s.dims();
+        sa.nblk = (int)small_blocks(s);
+        sa.iter0 = iter0;
+        sa.wait_ticks = ticks;
+        void *args[] = {&sa};
+        HIPCHK(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_pcg_small<T, NR>),
+                                          dim3((unsigned)sa.nblk), dim3(kSmallThreads), args, 0, st));
+    }
+    if (work && !cell_per_thread) {
         PersistArgs<T, NR> pa{};
         IterArgs<T> &a = pa.it;
         a.cr = c[0];
@@ -964,15 +1006,14 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         pa.ctl = cx.ctl;
         pa.sync = cx.sync;
         pa.iter0 = iter0;
-        int dev = 0, khz = 0;
-        HIPCHK(hipGetDevice(&dev));
-        HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
-        pa.wait_ticks = (uint64_t)((double)khz * 1000.0 * kPersistWaitSec);
+        pa.wait_ticks = ticks;
         void *args[] = {&pa};
         HIPCHK(hipLaunchCooperativeKernel(persist_kernel<T, NR>(V), dim3((unsigned)a.nblk),
                                           dim3(kWave * kTJ), args, 0, st));
     }
-    int e = launch_catchup<T, NR>(cx, v, iter0);
+    // k_pcg_small leaves x complete
+    int e = MAS_OK;
+    if (!cell_per_thread) e = launch_catchup<T, NR>(cx, v, iter0);
     if (e != MAS_OK) return e;
     if (watch.rep.box && work) {
         e = wait_report(cx, [&] {
@@ -1008,7 +1049,7 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     {
         const int pc = persist_choice<T, NR>(cx, v, iter0);
         if (pc < 0) return pc;
-        if (pc == 1) return run_pcg_persist<T, NR>(cx, v, c, mode, iter0, check_every, res);
+        if (pc > 0) return run_pcg_persist<T, NR>(cx, v, c, mode, iter0, check_every, pc == 2, res);
     }
     cx.launched = MAS_LAUNCH_PER_ITERATION;
     const mas_op *op = cx.op;

@@ -168,3 +168,31 @@ def test_persistent_requests_refused():
     _, op2 = gpu_operator(q)
     with pytest.raises(abi.MasError, match="do not fit"):
         op2.solve(to_dev(q.rhs), S.make_opts(launch="persistent", chunk_planes=1))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+@pytest.mark.parametrize("shape", [(1, 3, 2), (8, 8, 8), (27, 19, 1), (3, 9, 19), (1, 512, 256), (64, 32, 64)])
+def test_cell_per_thread_matches_oracle(shape, precision):
+    """A run with a cell per thread at the edges of its range: six cells, one
+    block exactly (512 cells), one cell more than a block, phi rings of one
+    cell and split between blocks, and all 256 blocks (2^17 cells); the
+    oracle's residual, its iterates, and three right-hand sides of which one
+    is zero and one starts at its solution."""
+    p = problem(shape, (0, 1))
+    _, op = gpu_operator(p, precision)
+    ora = oracle_operator(p)
+    rhs, b = to_dev(p.rhs), ora.rhs_to_b(p.rhs)
+    o = S.make_opts(rtol=1e-10, precision=precision)
+    x, info = op.solve(rhs, o, allow_notconv=False)
+    assert info["launch"] == abi.MAS_LAUNCH_PERSISTENT
+    assert ora.rel_residual(b, to_host(x)) <= 1e-10
+    if precision == "fp64":
+        for k in (1, 4):
+            y, _ = op.solve(rhs, S.make_opts(rtol=0.0, max_iters=k, max_restarts=0))
+            yo = ora.pcg(b, tol=0.0, max_iters=k)[0]
+            assert np.linalg.norm(to_host(y) - yo) <= 1e-11 * k * max(np.linalg.norm(yo), 1e-300)
+    three = torch.stack([rhs, torch.zeros_like(rhs), rhs])
+    X, infos = op.solve_multi(three, o, x0=torch.stack([torch.zeros_like(x), torch.zeros_like(x), x]),
+                              allow_notconv=False)
+    assert ora.rel_residual(b, to_host(X[0])) <= 1e-10 and ora.rel_residual(b, to_host(X[2])) <= 1e-10
+    assert not X[1].any() and infos[2]["iters"] <= 1
