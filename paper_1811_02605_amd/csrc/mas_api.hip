@@ -71,6 +71,7 @@ static constexpr int kTI = MAS_TI;
 #ifndef MAS_SMALL_TI
 #define MAS_SMALL_TI 1
 #endif
+static constexpr int64_t kCUs = 256;  // compute units of the device
 static constexpr int64_t kMinBlocks = MAS_MIN_BLOCKS;
 static constexpr int kSmallTI = MAS_SMALL_TI;
 
@@ -88,10 +89,11 @@ static constexpr int vec_full() {
     constexpr int bytes = sizeof(T) == 8 ? MAS_ITER_VEC : MAS_ITER_VEC_F32;
     return bytes / (int)sizeof(T) > 0 ? bytes / (int)sizeof(T) : 1;
 }
+// a row of at most v cells that is not exactly v keeps one cell per lane
 template <typename T>
 static inline int vec_width(int np) {
     constexpr int v = vec_full<T>();
-    return (np % v == 0) ? v : 1;
+    return (np >= v) ? v : 1;
 }
 
 // Lanes' vector width of the iteration kernel for nrhs right-hand sides.
@@ -148,25 +150,54 @@ struct Shape {
     int nr, nt, np;
     int64_t plane, n;
     Dims dims() const { return Dims{nr, nt, np, plane, n}; }
-    int tiles_k(int v) const { return (np + (kWave / kRPW) * v - 1) / ((kWave / kRPW) * v); }
+    // phi cells per segment of the iteration kernel with v cells per lane: a
+    // whole half-wave of lanes, or, where the row's last lane overlaps the one
+    // before (np no multiple of v), as many lanes as share the row about evenly
+    // between as few segments, so that the last segment holds both
+    int seg(int v) const {
+        const int most = kWave / kRPW, lanes = (np + v - 1) / v;
+        if (v == 1 || np % v == 0) return most * v;
+        const int segs = (lanes + most - 1) / most;
+        int wl = (lanes + segs - 1) / segs;
+        while (wl > 2 && lanes - ((lanes + wl - 1) / wl - 1) * wl < 2) --wl;
+        return wl * v;
+    }
+    int tiles_k(int v) const { return (np + seg(v) - 1) / seg(v); }
     int tiles_j() const { return (nt + kTJ * kRPW - 1) / (kTJ * kRPW); }
-    // r planes per chunk: the tiles of one chunk are consecutive logical
-    // blocks, and xcd_remap hands each of the 8 XCDs a contiguous eighth of
-    // them, so with 8 chunks (or a multiple) every XCD owns whole r slabs
-    // and only the planes at slab boundaries are read by two XCDs (256 x 320
-    // x 640 cells: 32-plane chunks, 1.4% faster than 16).  At least kTI
-    // planes, unless that leaves fewer than kMinBlocks blocks: a small grid
-    // is latency-bound (each wave's plane steps run one after another), so
-    // its chunks shrink, down to kSmallTI planes, until about kMinBlocks
-    // blocks share the work.
+    // r planes per chunk of the iteration kernel: the tiles of one chunk are
+    // consecutive logical blocks, and xcd_remap hands each of the 8 XCDs a
+    // contiguous eighth of them, so with 8 chunks (or a multiple) every XCD owns
+    // whole r slabs and only the planes at slab boundaries are read by two XCDs
+    // (256 x 320 x 640 cells: 32-plane chunks, 1.4% faster than 16), at least
+    // kTI planes.  A grid with fewer than eight such blocks per CU is bound by
+    // the plane steps of the CU with the most blocks: t + 2 steps, each as long
+    // as a wait for memory and twice that for every block that shares the CU
+    // (64 x 96 x 192 cells: 1.8 us with one block on a CU, 3.1, 4.2 and 5.2 with
+    // two, three and four); the t that makes that shortest.  us per iteration,
+    // against about 1024 blocks whatever the CUs: 64 x 96 x 192 cells 29.4 (33),
+    // 40 x 56 x 112 14.9 (15.6), 128 x 192 x 384 in single precision 79.5 (86.8).
     // (a forced chunk, or the rule's, capped by max_chunk)
     int ti(int v, int forced = 0) const {
         const int cap = max_chunk(iter_plane_bytes(v));
         if (forced > 0) return std::min(forced, cap);
-        return std::min(chunk_for((int64_t)tiles_k(v) * tiles_j()), cap);
+        const int64_t tiles = (int64_t)tiles_k(v) * tiles_j();
+        const int big = std::max(kTI, (nr + 7) / 8);
+        if (tiles * ((nr + big - 1) / big) >= 8 * kCUs) return std::min(big, cap);
+        int best = 1;
+        int64_t cost = INT64_MAX;
+        for (int t = 1; t <= std::min(nr, cap); ++t) {
+            const int64_t per_cu = (tiles * ((nr + t - 1) / t) + kCUs - 1) / kCUs;
+            if ((t + 2) * (1 + 2 * per_cu) < cost) {
+                cost = (t + 2) * (1 + 2 * per_cu);
+                best = t;
+            }
+        }
+        return best;
     }
-    // the same rule for any marching kernel with `tiles` tiles per plane
-    // (arrays of 8-byte elements)
+    // the other marching kernels with `tiles` tiles per plane (arrays of 8-byte
+    // elements): r slabs as above, unless that leaves fewer than kMinBlocks
+    // blocks: then their chunks shrink, down to kSmallTI planes, until about
+    // kMinBlocks blocks share the work
     int chunk_for(int64_t tiles) const {
         const int big = std::max(kTI, (nr + 7) / 8);
         int t;
@@ -200,9 +231,8 @@ struct Shape {
     // whether the records can be used (every segment spans two lanes)
     int64_t halo_bytes(int v, int64_t es) const { return (int64_t)nr * nt * tiles_k(v) * 2 * 4 * es; }
     bool halo_ok(int v) const {
-        const int seg = (kWave / kRPW) * v;
-        const int last = np - (tiles_k(v) - 1) * seg;
-        return last >= 2 * v;
+        const int last = np - (tiles_k(v) - 1) * seg(v);
+        return v > 1 && last > v;
     }
     dim3 simple_grid() const {
         return dim3((np + kWave - 1) / kWave, (nt + kSimpleJ - 1) / kSimpleJ,
@@ -866,10 +896,11 @@ static int persist_chunk(const Ctx &cx, int V) {
 }
 
 template <typename T, int NR>
-static const void *persist_kernel(int V) {
+static const void *persist_kernel(int V, int np) {
     constexpr int VW = vec_full<T>();
-    return (V == VW) ? reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, VW>)
-                     : reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, 1>);
+    if (V == 1) return reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, 1, false>);
+    return np % VW ? reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, VW, true>)
+                   : reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, VW, false>);
 }
 
 // Whether a PC1 run of NR right-hand sides goes into one persistent launch
@@ -900,7 +931,7 @@ static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
                                                             kSmallThreads, 0));
         if ((int64_t)per_cu * ncu >= small_blocks(s)) return 2;
     }
-    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_kernel<T, NR>(V), kWave * kTJ, 0));
+    HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_kernel<T, NR>(V, s.np), kWave * kTJ, 0));
     if ((int64_t)per_cu * ncu < nblk) return no("the iteration kernel's blocks do not fit on the GPU at once");
     return 1;
 }
@@ -921,6 +952,27 @@ static void start_run(Ctx &cx, const RhsSet<T> &v, int mode, int iter0, int chec
         in.beta0[h] = v.keep_p[h] ? v.beta0[h] : 0.0;
     }
     hipLaunchKernelGGL(k_run_init, dim3(1), dim3(256), 0, cx.stream, cx.ctl, cx.sync, in);
+}
+
+// One launch of the iteration kernel for NR right-hand sides with vector width
+// V (vec_full, or 1 for the shortest rows), reading segment-edge records (halo)
+// or edge cells.
+template <typename T, int NR>
+static void launch_iter(const IterArgs<T> &a, bool halo, int V, hipStream_t st) {
+    constexpr int VW = vec_full<T>();
+    auto go = [&](auto vw, auto hl, auto rag) {
+        hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, decltype(vw)::value, decltype(hl)::value, decltype(rag)::value>),
+                           dim3((unsigned)a.nblk), dim3(kWave * kTJ), 0, st, a);
+    };
+    using F = std::false_type;
+    using Tr = std::true_type;
+    using IW = std::integral_constant<int, VW>;
+    if (V == 1)
+        go(std::integral_constant<int, 1>{}, F{}, F{});
+    else if (a.d.np % VW)
+        halo ? go(IW{}, Tr{}, Tr{}) : go(IW{}, F{}, Tr{});
+    else
+        halo ? go(IW{}, Tr{}, F{}) : go(IW{}, F{}, F{});
 }
 
 static int persist_gave_up() {
@@ -989,6 +1041,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         a.tiles_k = s.tiles_k(V);
         a.tiles_j = s.tiles_j();
         a.ti = s.ti(V, ch);
+        a.seg = s.seg(V);
         a.nblk = (int)s.nblk_iter(V, ch);
         a.records = 0;
         a.rep = watch.rep;
@@ -1008,7 +1061,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         pa.iter0 = iter0;
         pa.wait_ticks = ticks;
         void *args[] = {&pa};
-        HIPCHK(hipLaunchCooperativeKernel(persist_kernel<T, NR>(V), dim3((unsigned)a.nblk),
+        HIPCHK(hipLaunchCooperativeKernel(persist_kernel<T, NR>(V, s.np), dim3((unsigned)a.nblk),
                                           dim3(kWave * kTJ), args, 0, st));
     }
     // k_pcg_small leaves x complete
@@ -1076,11 +1129,11 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     a.tiles_k = s.tiles_k(V);
     a.tiles_j = s.tiles_j();
     a.ti = s.ti(V, cx.chunk);
+    a.seg = s.seg(V);
     a.nblk = (int)s.nblk_iter(V, cx.chunk);
     for (int h = 0; h < NR; ++h) a.x[h] = v.x[h];
     a.records = v.records ? 1 : 0;
     const bool use_halo = v.records;
-    const dim3 grid((unsigned)a.nblk), block(kWave * kTJ);
 
     for (int k = iter0; k <= max_iter; ++k) {
         int e = watch.room(k, iter0);
@@ -1119,20 +1172,7 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
             cx.ev_iter.push_back(k);
             HIPCHK(hipEventRecord(e0, st));
         }
-        constexpr int VW = vec_full<T>();
-        auto go = [&](auto vw, auto hl) {
-            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, decltype(vw)::value,
-                                           decltype(hl)::value>),
-                               grid, block, 0, st, a);
-        };
-        using F = std::false_type;
-        using Tr = std::true_type;
-        using IW = std::integral_constant<int, VW>;
-        using I1 = std::integral_constant<int, 1>;
-        if (V == VW)
-            halo ? go(IW{}, Tr{}) : go(IW{}, F{});
-        else
-            halo ? go(I1{}, Tr{}) : go(I1{}, F{});
+        launch_iter<T, NR>(a, halo, V, st);
         if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
         LAUNCHCHK();
     }
@@ -1252,6 +1292,7 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     it.tiles_k = s.tiles_k(V);
     it.tiles_j = s.tiles_j();
     it.ti = s.ti(V, cx.chunk);
+    it.seg = s.seg(V);
     it.nblk = (int)s.nblk_iter(V, cx.chunk);
     it.records = 0;
     for (int h = 0; h < NR; ++h) {
@@ -1269,8 +1310,6 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
     // z = M^-1 r of the initial residuals, (r, z), the stopping tests
     solve_all(1);
     LAUNCHCHK();
-    constexpr int VW = vec_full<T>();
-    const dim3 igrid((unsigned)it.nblk), iblock(kWave * kTJ);
     for (int k = iter0; k < kmax; ++k) {
         const int e = watch.room(k, iter0);
         if (e != MAS_OK) return e;
@@ -1291,12 +1330,7 @@ static int run_pcg_pc2(Ctx &cx, const Pc2Vecs<T, NR> &v, const bool active[NR], 
             it.p_out[h] = v.p[h][(k + 1) & 1];
         }
         it.xstep = (k - iter0 >= 2 && ((k - iter0) & 1) == 0) ? 1 : 0;
-        if (V == VW)
-            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, VW, false>), igrid, iblock,
-                               0, st, it);
-        else
-            hipLaunchKernelGGL((k_pcg_iter<T, NR, kTJ, kRPW, 1, false>), igrid, iblock,
-                               0, st, it);
+        launch_iter<T, NR>(it, false, V, st);
         solve_all(0);
         if (sample) HIPCHK(hipEventRecord(cx.ev.back(), st));
         LAUNCHCHK();

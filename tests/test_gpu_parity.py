@@ -349,3 +349,28 @@ def test_probe_copy():
     S.probe_copy(src, dst)
     torch.cuda.synchronize()
     assert torch.equal(src, dst)
+
+
+# rows that are no multiple of the lanes' vector width (2 doubles, 4 floats): two
+# lanes, one lane short of and one past a 32-lane segment, segments shared
+# evenly, and the widths whose last segment would hold a single lane
+@pytest.mark.parametrize("np_", [3, 5, 6, 7, 63, 65, 127, 129, 130, 131, 1985, 3971])
+@pytest.mark.parametrize("chunk", [0, 2])
+def test_ragged_rows_launched_per_iteration(np_, chunk):
+    p = problem((3, 9, np_), (1, 0))
+    _, op = gpu_operator(p, "fp32_refined")
+    ora = oracle_operator(p)
+    rhs, b = to_dev(p.rhs), ora.rhs_to_b(p.rhs)
+    two = torch.stack([rhs, rhs.flip(2).contiguous()])
+    for k in (1, 2, 5):
+        o = S.make_opts(rtol=0.0, max_iters=k, max_restarts=0, launch="per_iteration", chunk_planes=chunk)
+        x, info = op.solve(rhs, o)
+        X, _ = op.solve_multi(two, o)
+        xo = ora.pcg(b, tol=0.0, max_iters=k)[0]
+        assert rel(to_host(x), xo) <= 1e-11 * k
+        assert torch.equal(X[0], x)
+    for precond in ("pc1", "pc2"):
+        o = S.make_opts(rtol=1e-10, precision="fp32_refined", precond=precond, launch="per_iteration" if precond == "pc1"
+                        else "auto", chunk_planes=chunk)
+        x, _ = op.solve(rhs, o, allow_notconv=False)
+        assert ora.rel_residual(b, to_host(x)) <= 1e-10
