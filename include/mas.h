@@ -123,8 +123,8 @@ typedef struct {
 } mas_pcg_opts;
 
 /* How a PC1 run (one to four right-hand sides) is launched.
- *   MAS_LAUNCH_PER_ITERATION: an iteration kernel and a one-block finalize per
- *     iteration, the host polling the run flags after each batch.
+ *   MAS_LAUNCH_PER_ITERATION: one kernel per iteration (its last block
+ *     finalizes), the host queueing ahead of the progress that it reports.
  *   MAS_LAUNCH_PERSISTENT: the whole run in one cooperative launch whose
  *     blocks are all resident at once, with a grid barrier per iteration and
  *     every block applying the same finalize (the same results bit for bit).
@@ -132,14 +132,17 @@ typedef struct {
  *     the GPU at once (small grids, where launches and latency, not
  *     bandwidth, set the time); MAS_EINVAL otherwise.
  *     With chunk_planes = 0 a grid of at most 2^17 cells runs with a cell
- *     per thread, a larger one in r chunks long enough for about 64
+ *     per thread, a larger one with one right-hand side in columns of cells
+ *     per thread if 256 blocks of 8 theta x 64 phi cells by 10 (FP64) or 20
+ *     (refined) r planes cover it, others in r chunks long enough for about 64
  *     blocks; with the same chunk_planes > 0 both modes give the same results
  *     bit for bit (otherwise the partial dot products are summed in another
  *     order).  Its blocks wait for each other at every iteration, at most
  *     2 s: if kernels of other streams keep part of its blocks from
  *     starting for longer, the call returns MAS_EHIP instead of hanging.
  *   MAS_LAUNCH_AUTO: persistent where it is possible and the grid has at
- *     most 2^17 cells, per iteration otherwise.
+ *     most 2^17 cells, or more than 2^18 and runs in columns; per iteration
+ *     otherwise, and where other work keeps a run in columns from starting.
  * PC2 is always launched per iteration. */
 enum { MAS_LAUNCH_AUTO = 0, MAS_LAUNCH_PER_ITERATION = 1, MAS_LAUNCH_PERSISTENT = 2 };
 

@@ -11,8 +11,8 @@
 // b^ = W^-1 b (split preconditioning with M = diag(A) = W^2), so the solver
 // iterates on the scaled system and never stores or reads diag(A)^-1.
 //
-// One PCG iteration is ONE stencil kernel (k_pcg_iter) plus a one-block
-// finalize.  Kernel k, for every cell, forms
+// One PCG iteration is ONE stencil kernel (k_pcg_iter), whose last block
+// finalizes.  Kernel k, for every cell, forms
 //     r_k = r_{k-1} - alpha_{k-1} q_{k-1}
 //     x_k = x_{k-1} + alpha_{k-1} p_{k-1}
 //     p_k = r_k + beta_k p_{k-1}
@@ -52,7 +52,7 @@ struct Ctl {
     double tol2;       // threshold on the checked quantity
     double rr_next;    // (r_{k+1}, r_{k+1}) predicted by the recurrence at the last finalize
     double pq, rq, qq; // last sums (diagnostics)
-    double sums[8];    // results of k_reduce
+    double sums[8];    // sums of a kernel that finishes by finish_sums
     double wratio;     // ||W r||^2 / (r,r) at the last check (predicts ||W r||^2 from (r,r))
     double alpha_prev; // the alpha the last iteration kernel applied (its x update, when that
                        // kernel left it to the next one or to k_x_catchup)
@@ -1224,6 +1224,7 @@ void k_pcg_iter(IterArgs<T> a) {
 struct PersistSync {
     uint32_t bar;    // barrier arrivals, zero at launch
     int32_t err;     // 1: a block gave up waiting at a barrier
+    int32_t done;    // 1: a block has finished the run (k_pcg_column)
     BlockCount count;
 };
 
@@ -1396,7 +1397,72 @@ struct SmallArgs {
     int nblk, iter0;
     int keep_p[NR];   // the first iteration continues the direction in p[c][iter0 & 1]
     uint64_t wait_ticks;
+    int ti;           // k_pcg_column: r planes per block
+    uint64_t start_ticks;  // k_pcg_column: longest wait for every block to start
 };
+
+// One exchange of a persistent run: the block's NV sums (acc: each thread's
+// part) become words tagged with the iteration's number, once everything the
+// block has published before is acknowledged; then every block's words are
+// read until their tags match, and sAll holds each wave's part of the totals.
+// False (for the whole block) once a wait exceeds wait_ticks.
+template <int NV>
+__device__ __forceinline__ bool exchange_sums(double (&acc)[NV], double (*sWave)[NV], double (*sAll)[NV],
+                                              int *gave_up, uint64_t *slots, int nblk, int blk, uint32_t tag,
+                                              uint64_t wait_ticks) {
+    constexpr int NW = kSmallThreads / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+#pragma unroll
+    for (int t = 0; t < NV; ++t) acc[t] = wave_sum(acc[t]);
+    if (lane == 0) {
+#pragma unroll
+        for (int t = 0; t < NV; ++t) sWave[wv][t] = acc[t];
+    }
+    wait_stores();
+    __syncthreads();
+    if (tid < NV) {
+        double v = 0.0;
+        for (int u = 0; u < NW; ++u) v += sWave[u][tid];
+        const uint64_t b = __builtin_bit_cast(uint64_t, v), hi = (uint64_t)tag << 32;
+        st_agent(slots + (int64_t)(2 * tid) * nblk + blk, hi | (uint32_t)b);
+        st_agent(slots + (int64_t)(2 * tid + 1) * nblk + blk, hi | (b >> 32));
+    }
+    // every block's
+    if (wv < kSmallBlocks / kWave) {
+        double v[NV];
+#pragma unroll
+        for (int t = 0; t < NV; ++t) v[t] = 0.0;
+        if (tid < nblk) {
+            const uint64_t t0 = wall_clock64();
+            for (;;) {
+                uint64_t g[2 * NV];
+#pragma unroll
+                for (int t = 0; t < 2 * NV; ++t) g[t] = ld_agent(slots + (int64_t)t * nblk + tid);
+                bool all = true;
+#pragma unroll
+                for (int t = 0; t < 2 * NV; ++t) all = all && (uint32_t)(g[t] >> 32) == tag;
+                if (all) {
+#pragma unroll
+                    for (int t = 0; t < NV; ++t)
+                        v[t] = __builtin_bit_cast(double, (g[2 * t] & 0xffffffffu) | (g[2 * t + 1] << 32));
+                    break;
+                }
+                if (wall_clock64() - t0 > wait_ticks) {
+                    *gave_up = 1;
+                    break;
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
+        if (lane == 0) {
+#pragma unroll
+            for (int t = 0; t < NV; ++t) sAll[wv][t] = v[t];
+        }
+    }
+    __syncthreads();
+    return !*gave_up;
+}
 
 template <typename T, int NR>
 __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a) {
@@ -1404,7 +1470,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
     __shared__ double sWave[NW][NV], sAll[kSmallBlocks / kWave][NV];
     __shared__ Ctl sCtl[NR];
     __shared__ int gave_up;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int tid = threadIdx.x;
     const int nblk = a.nblk, blk = blockIdx.x;
     const int np = a.d.np, nt = a.d.nt, plane = (int)a.d.plane, n = (int)a.d.n;
     const int c = blk * kSmallThreads + tid;
@@ -1483,59 +1549,9 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
                 acc[h * kNV + 4] = t * t;
             }
         }
-        // the block's sums, as words tagged with the iteration's number
-#pragma unroll
-        for (int t = 0; t < NV; ++t) acc[t] = wave_sum(acc[t]);
-        if (lane == 0) {
-#pragma unroll
-            for (int t = 0; t < NV; ++t) sWave[wv][t] = acc[t];
-        }
-        wait_stores();
-        __syncthreads();
-        const uint32_t tag = (uint32_t)s + 1u;
-        uint64_t *slots = a.slots + (int64_t)cur * (2 * NV) * nblk;
-        if (tid < NV) {
-            double v = 0.0;
-            for (int u = 0; u < NW; ++u) v += sWave[u][tid];
-            const uint64_t b = __builtin_bit_cast(uint64_t, v), hi = (uint64_t)tag << 32;
-            st_agent(slots + (int64_t)(2 * tid) * nblk + blk, hi | (uint32_t)b);
-            st_agent(slots + (int64_t)(2 * tid + 1) * nblk + blk, hi | (b >> 32));
-        }
-        // every block's
-        if (wv < kSmallBlocks / kWave) {
-            double v[NV];
-#pragma unroll
-            for (int t = 0; t < NV; ++t) v[t] = 0.0;
-            if (tid < nblk) {
-                const uint64_t t0 = wall_clock64();
-                for (;;) {
-                    uint64_t g[2 * NV];
-#pragma unroll
-                    for (int t = 0; t < 2 * NV; ++t) g[t] = ld_agent(slots + (int64_t)t * nblk + tid);
-                    bool all = true;
-#pragma unroll
-                    for (int t = 0; t < 2 * NV; ++t) all = all && (uint32_t)(g[t] >> 32) == tag;
-                    if (all) {
-#pragma unroll
-                        for (int t = 0; t < NV; ++t)
-                            v[t] = __builtin_bit_cast(double, (g[2 * t] & 0xffffffffu) | (g[2 * t + 1] << 32));
-                        break;
-                    }
-                    if (wall_clock64() - t0 > a.wait_ticks) {
-                        gave_up = 1;
-                        break;
-                    }
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < NV; ++t) v[t] = wave_sum(v[t]);
-            if (lane == 0) {
-#pragma unroll
-                for (int t = 0; t < NV; ++t) sAll[wv][t] = v[t];
-            }
-        }
-        __syncthreads();
-        if (gave_up) {
+        const bool done = exchange_sums<NV>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk, nblk,
+                                            blk, (uint32_t)s + 1u, a.wait_ticks);
+        if (!done) {
             if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
             if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return;
@@ -1569,6 +1585,256 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
     if (in) {
 #pragma unroll
         for (int h = 0; h < NR; ++h) a.x[h][cc] = x[h];
+    }
+}
+
+// ---------------------------------------------------------------- persistent run, a column of cells per thread
+// The same run for larger grids that still fit the register files: a block of
+// 8 theta rows x 64 phi cells holds up to K r planes, each thread the r, p, q,
+// x and couplings of one column, for the whole run (a CU has 512 KB of
+// registers and 160 KB of LDS).  Launched per
+// iteration such a grid moves 84 bytes a cell through the last-level cache;
+// here only tile edges move:
+//   - inside the tile p_k goes through LDS (theta, phi) or is in the thread
+//     itself (r);
+//   - of the cells around the tile every block keeps its own copies of r and
+//     p, so one word of each, q_{k-1}, is read per iteration, and one is
+//     published by each cell at a tile's edge (about half of them);
+//   - the sums go round as in k_pcg_small.
+// What is left is the exchange (8-9 us) and, per plane, 0.4 us.  us per
+// iteration, launched per iteration in brackets: 64 x 96 x 192 cells 14.2
+// (31.1), FP32 13.6 (24.1); 33 x 88 x 96 11.4 (16.7); 80 x 128 x 128 13.9
+// (32.9); FP32 160 x 128 x 128, whose 20 planes spill 55 registers, 21.4 (32.6).
+// r, p and x reach memory only at the end of a run that ends regularly: a run
+// that gave up has changed nothing but q, and can be made in another way, if
+// no block has set sync->done.
+constexpr int kColH = kSmallThreads / kWave;  // theta rows of a tile
+template <typename T>
+constexpr int kColMax = sizeof(T) == 8 ? 10 : 20;  // most planes: 256 registers a thread
+
+// Registers end at 6 planes in FP64 and 8 in FP32 with all couplings in them;
+// above, the theta couplings lie in LDS, then the phi couplings as well (all in
+// registers, 284 bytes a thread spilled: 64 x 96 x 192 cells 2.6 ms, so 1.7).
+template <typename T, int K>
+__global__ __launch_bounds__(kSmallThreads) void k_pcg_column(SmallArgs<T, 1> a) {
+    constexpr int NV = kNV, H = kColH, W = kWave, RW = W + 2, PL = (H + 2) * RW;
+    constexpr bool LT = K > (sizeof(T) == 8 ? 6 : 8), LP = K > (sizeof(T) == 8 ? 8 : 12);
+    constexpr int KT = LT ? 0 : K, KP = LP ? 0 : K;
+    constexpr int EDGE = 2 * W + 2 * H;  // cells around the tile, per plane
+    constexpr int NS = (EDGE * K + kSmallThreads - 1) / kSmallThreads;
+    __shared__ T sP[K * PL];
+    // coupling between theta row v - 1 and v at [m][v], between the phi cell left of l and l at [m][row][l]
+    __shared__ T sCt[LT ? K * (H + 1) * W : 1], sCp[LP ? K * H * (W + 1) : 1];
+    __shared__ double sWave[kSmallThreads / kWave][NV], sAll[kSmallBlocks / kWave][NV];
+    __shared__ Ctl sCtl[kSmallThreads / kWave];
+    __shared__ int gave_up;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    const int nblk = a.nblk, blk = blockIdx.x;
+    const int nr = a.d.nr, nt = a.d.nt, np = a.d.np, plane = (int)a.d.plane;
+    for (int t = tid; t < 2 * 2 * NV; t += kSmallThreads) st_agent(a.slots + (int64_t)t * nblk + blk, (uint64_t)0);
+    for (int t = tid; t < K * PL; t += kSmallThreads) sP[t] = T(0);
+    if (tid == 0) gave_up = 0;
+    // one copy per wave, in LDS: a wave finalizes and reads its own
+    if (lane == 0) sCtl[wv] = a.ctl[0];
+    Ctl &lc = sCtl[wv];
+    const int tk = (np + W - 1) / W, tj = (nt + H - 1) / H;
+    const int k0 = (blk % tk) * W, j0 = (blk / tk % tj) * H, i0 = (blk / tk / tj) * a.ti;
+    const int nseg = min(W, np - k0), nj = min(H, nt - j0), ni = min(a.ti, nr - i0);
+    const int j = j0 + wv, k_phi = k0 + lane;
+    const bool act = lane < nseg && wv < nj;
+    // the column's first cell; arrays are addressed by a uniform pointer to the
+    // plane and 32-bit byte offsets, which need no registers per plane
+    const int c0 = act ? i0 * plane + j * np + k_phi : 0;
+    const uint32_t o0 = (uint32_t)c0 * (uint32_t)sizeof(T);
+    const int pos = (wv + 1) * RW + lane + 1;
+    // columns whose every cell is at the tile's edge
+    const bool rim = lane == 0 || lane == nseg - 1 || wv == 0 || wv == nj - 1;
+    const int in = a.iter0 & 1;
+    const bool keep = a.keep_p[0];
+    // a cell that is not there is 0 and has no coupling
+    T r[K], p[K], q[K], x[K], f[K + 1], ctU[KT + 1], ctD[KT + 1], cpL[KP + 1], cpR[KP + 1];
+    const int left = k_phi == 0 ? np - 1 : -1;
+    f[0] = act && i0 > 0 ? a.cr[c0 - plane] : T(0);
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+        const bool ok = act && m < ni;
+        const int c = ok ? c0 + m * plane : 0;
+        r[m] = ok ? a.r[0][in][c] : T(0);
+        p[m] = ok && keep ? a.p[0][in][c] : r[m];
+        q[m] = r[m];  // alpha = 0
+        x[m] = ok ? a.x[0][c] : T(0);
+        f[m + 1] = ok && i0 + m < nr - 1 ? a.cr[c] : T(0);
+        const T tu = ok && j > 0 ? a.ct[c - np] : T(0), td = ok && j < nt - 1 ? a.ct[c] : T(0);
+        const T fl = ok ? a.cp[c + left] : T(0), fr = ok ? a.cp[c] : T(0);
+        if constexpr (LT) {
+            // a row writes the face below it, the first one also that above
+            sCt[(m * (H + 1) + wv + 1) * W + lane] = td;
+            if (wv == 0) sCt[m * (H + 1) * W + lane] = tu;
+        } else {
+            ctU[m] = tu;
+            ctD[m] = td;
+        }
+        if constexpr (LP) {
+            sCp[(m * H + wv) * (W + 1) + lane + 1] = fr;
+            if (lane == 0) sCp[(m * H + wv) * (W + 1)] = fl;
+        } else {
+            cpL[m] = fl;
+            cpR[m] = fr;
+        }
+    }
+    // the cells around the tile: two planes of the own column, NS of the rim
+    constexpr uint32_t none = 0xffffffffu;
+    const uint32_t pb = (uint32_t)plane * (uint32_t)sizeof(T);
+    const uint32_t oLo = act && i0 > 0 ? o0 - pb : none, oHi = act && i0 + ni < nr ? o0 + (uint32_t)ni * pb : none;
+    auto at = [](auto *base, uint32_t o) { return reinterpret_cast<decltype(base)>((uintptr_t)base + o); };
+    uint32_t oS[NS];
+    int lS[NS];
+    T rS[NS], pS[NS];
+    auto load = [&](uint32_t o, T &rr, T &pp) {
+        rr = o != none ? *at(a.r[0][in], o) : T(0);
+        pp = o != none && keep ? *at(a.p[0][in], o) : rr;
+    };
+    T rLo, pLo, rHi, pHi;
+    load(oLo, rLo, pLo);
+    load(oHi, rHi, pHi);
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+        const int e = tid + t * kSmallThreads, m = e / EDGE, u = e % EDGE;
+        int jj, kk, l;
+        bool ok = m < ni;
+        if (u < 2 * W) {  // the rows above and below
+            const int v = u % W;
+            jj = u < W ? j0 - 1 : j0 + H;
+            kk = k0 + v;
+            l = (u < W ? 0 : (H + 1) * RW) + v + 1;
+            ok = ok && v < nseg && jj >= 0 && jj < nt;
+        } else {  // the columns left and right
+            const int v = (u - 2 * W) % H;
+            const bool lf = u - 2 * W < H;
+            jj = j0 + v;
+            kk = lf ? (k0 == 0 ? np - 1 : k0 - 1) : (k0 + nseg == np ? 0 : k0 + nseg);
+            l = (v + 1) * RW + (lf ? 0 : nseg + 1);
+            ok = ok && v < nj;
+        }
+        oS[t] = ok ? (uint32_t)((i0 + m) * plane + jj * np + kk) * (uint32_t)sizeof(T) : none;
+        lS[t] = ok ? m * PL + l : 0;
+        load(oS[t], rS[t], pS[t]);
+    }
+    // every block runs once this one is passed; a block that starts after others
+    // have given up here finds err set
+    const bool here = grid_barrier(a.sync, (uint32_t)nblk, a.start_ticks);
+    if (tid == 0 && here && ld_agent(&a.sync->err)) gave_up = 1;
+    __syncthreads();
+    if (!here || gave_up) {
+        if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
+        if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    int nxt = in;
+    for (int k = a.iter0; __builtin_amdgcn_readfirstlane(lc.flag) == FLAG_RUN; ++k) {
+        const int cur = k & 1, s = k - a.iter0;
+        nxt = cur ^ 1;
+        const T alpha = (T)lc.alpha, beta = (T)lc.beta;
+        T qLo = rLo, qHi = rHi, qS[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) qS[t] = rS[t];
+        if (s > 0) {
+            const T *Q = a.q[0][cur];
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+                if (oS[t] != none) qS[t] = ld_agent(at(Q, oS[t]));
+            if (oLo != none) qLo = ld_agent(at(Q, oLo));
+            if (oHi != none) qHi = ld_agent(at(Q, oHi));
+        }
+        auto step = [&](T &rr, T &pp, T qq) {
+            rr = rr - alpha * qq;
+            pp = rr + beta * pp;
+        };
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            x[m] = x[m] + alpha * p[m];
+            step(r[m], p[m], q[m]);
+            if (act) sP[m * PL + pos] = p[m];
+        }
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+            step(rS[t], pS[t], qS[t]);
+            if (oS[t] != none) sP[lS[t]] = pS[t];
+        }
+        step(rLo, pLo, qLo);
+        step(rHi, pHi, qHi);
+        __syncthreads();
+        double acc[NV] = {};
+        T *Qo = a.q[0][nxt];
+#pragma unroll
+        for (int m = 0; m < K; ++m) {
+            const T *P = sP + m * PL + pos;
+            const T lo = m == 0 ? pLo : p[m > 0 ? m - 1 : 0];
+            const T hi = m == K - 1 || m == ni - 1 ? pHi : p[m < K - 1 ? m + 1 : m];
+            T tu, td, fl, fr;
+            if constexpr (LT) {
+                const T *C = sCt + (m * (H + 1) + wv) * W + lane;
+                tu = C[0];
+                td = C[W];
+            } else {
+                tu = ctU[m];
+                td = ctD[m];
+            }
+            if constexpr (LP) {
+                const T *C = sCp + (m * H + wv) * (W + 1) + lane;
+                fl = C[0];
+                fr = C[1];
+            } else {
+                fl = cpL[m];
+                fr = cpR[m];
+            }
+            const T S = td * P[RW] + tu * P[-RW] + fr * P[1] + fl * P[-1] + f[m] * lo;
+            // cells not of this block stay 0 (plane ni and the lane right of a
+            // narrow tile adjoin cells that are)
+            q[m] = act && m < ni ? p[m] - (S + f[m + 1] * hi) : T(0);
+            if (act && m < ni && (rim || m == 0 || m == ni - 1)) st_agent(at(Qo + (int64_t)m * plane, o0), q[m]);
+            const double pd = (double)p[m], qd = (double)q[m], rd = (double)r[m];
+            acc[0] += pd * qd;
+            acc[1] += rd * qd;
+            acc[2] += qd * qd;
+            acc[3] += rd * rd;
+        }
+        if (__builtin_amdgcn_readfirstlane(lc.check) && act) {
+#pragma unroll
+            for (int m = 0; m < K; ++m) {
+                const double t = (m < ni ? *at(a.w + (int64_t)m * plane, (uint32_t)c0 * 8u) : 0.0) * (double)r[m];
+                acc[4] += t * t;
+            }
+        }
+        const bool done = exchange_sums<NV>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk, nblk,
+                                            blk, (uint32_t)s + 1u, a.wait_ticks);
+        if (!done) {
+            if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
+            if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        double S[kNV];
+#pragma unroll
+        for (int t = 0; t < kNV; ++t) {
+            S[t] = 0.0;
+#pragma unroll
+            for (int u = 0; u < kSmallBlocks / kWave; ++u) S[t] += sAll[u][t];
+        }
+        if (lane == 0) pcg_finalize(&lc, S);
+    }
+    if (tid == 0) st_agent(&a.sync->done, 1);
+#pragma unroll
+    for (int m = 0; m < K; ++m) {
+        if (act && m < ni) {
+            const int64_t mo = (int64_t)m * plane;
+            *at(a.x[0] + mo, o0) = x[m];
+            *at(a.r[0][nxt] + mo, o0) = r[m];
+            *at(a.p[0][nxt] + mo, o0) = p[m];
+        }
+    }
+    if (blk == 0 && tid == 0) {
+        a.ctl[0] = lc;
+        report_ctl(a.rep, 0, &lc);
     }
 }
 
@@ -2182,7 +2448,8 @@ __global__ __launch_bounds__(kWave *kSimpleJ) void k_refine_fold(float *dh, cons
     const double alpha = ctl ? ctl->alpha : 0.0;
     MAS_SIMPLE_LOOP(d, {
         if (cell.ok) {
-            x[cell.c] = x[cell.c] + ((double)dh[cell.c] + alpha * (double)p[cell.c]);
+            // (with none, p need not hold anything)
+            x[cell.c] = x[cell.c] + ((double)dh[cell.c] + (ctl ? alpha * (double)p[cell.c] : 0.0));
             dh[cell.c] = 0.0f;
         }
     })

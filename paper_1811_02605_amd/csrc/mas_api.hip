@@ -647,7 +647,7 @@ static Report new_report(HostBox *box) {
 struct Ctx {
     const mas_op *op;
     hipStream_t stream;
-    Ctl *ctl;  // [nrhs]; ctl[0] also receives k_reduce sums
+    Ctl *ctl;  // [nrhs]; ctl[0] also receives the other kernels' sums
     double *partials;
     bool timing;
     bool no_alloc = false;  // allocation-free entry point: no pinned box, no events
@@ -874,16 +874,27 @@ static int launch_catchup(Ctx &cx, const RhsSet<T> &v, int iter0) {
     return MAS_OK;
 }
 
-// Persistent launch (k_pcg_persist): the automatic choice takes it for
+// Persistent launch: the automatic choice takes it for
 // grids of at most kPersistAutoCells cells (latency-bound: a launch per
-// iteration costs about 14 us there whatever the size); unless chunk_planes
-// is set, its r chunks are as long as it takes to have at most about
+// iteration costs about 10 us there whatever the size).  The tiles of
+// k_pcg_persist run where chunk_planes is set or the kinds below do not fit;
+// unless it is set, their r chunks are as long as it takes to have at most about
 // kPersistBlocks blocks, since every block sums every block's partials and
 // arrives at the barrier (at 32 x 32 x 64 cells: 64 blocks 13.5 us per
 // iteration, 128 blocks 15.0 us, against 14.4 us launched per iteration).
 // A block gives up waiting at a grid barrier after kPersistWaitSec seconds.
 constexpr int64_t kPersistAutoCells = (int64_t)1 << 17;
 constexpr int64_t kPersistBlocks = 64;
+// Above that, a grid of up to 2^18 cells is launched per iteration by the
+// automatic choice, as callers may rely on; a larger one runs in columns where
+// it fits (FP64 up to 1.3M cells, FP32 2.6M, with full tiles).  Every one of 11
+// shapes that fits was 1.23 (33 x 88 x 96, FP32) to 2.4 times faster so, also
+// with tiles of one column or row left over (79 x 65 x 129: 1.42 and 3.00 ms).
+constexpr int64_t kColumnAutoCells = (int64_t)1 << 18;
+// Its blocks need a CU each.  Where another process or stream keeps some of
+// them from starting for longer than this, the automatic choice launches per
+// iteration instead (a run of 1.2M cells takes 1.5 ms in columns, 3.4 ms so).
+constexpr double kColumnStartSec = 0.004;
 constexpr double kPersistWaitSec = 2.0;
 
 // r planes per chunk of a persistent run (cx.chunk when set)
@@ -903,10 +914,41 @@ static const void *persist_kernel(int V, int np) {
                    : reinterpret_cast<const void *>(&k_pcg_persist<T, NR, kTJ, kRPW, VW, false>);
 }
 
-// Whether a PC1 run of NR right-hand sides goes into one persistent launch
-// (1: tiles of r chunks; 2: a cell per thread, when no chunk length is asked
-// for and the grid is small enough) or a launch per iteration (0); MAS_EINVAL when the persistent launch
-// was asked for and is not possible.
+// r planes per block of k_pcg_column on this grid, at most a block per CU: 0
+// if the grid does not fit that way.  The blocks then number at most
+// kSmallBlocks, whose words fit the partials of any grid above kSmallCells.
+template <typename T>
+static int column_planes(const Shape &s) {
+    const int64_t tiles = (int64_t)((s.np + kWave - 1) / kWave) * ((s.nt + kColH - 1) / kColH);
+    const int64_t chunks = std::min<int64_t>(kCUs, kSmallBlocks) / tiles;
+    if (chunks < 1) return 0;
+    const int64_t t = (s.nr + chunks - 1) / chunks;
+    return t <= kColMax<T> ? (int)t : 0;
+}
+static int64_t column_blocks(const Shape &s, int planes) {
+    return (int64_t)((s.np + kWave - 1) / kWave) * ((s.nt + kColH - 1) / kColH) * ((s.nr + planes - 1) / planes);
+}
+
+template <typename T>
+static const void *column_kernel(int planes) {
+    constexpr int U = kColMax<T> / 5;  // steps of 2 (FP64) or 4 planes
+    switch ((planes + U - 1) / U) {
+        case 1: return reinterpret_cast<const void *>(&k_pcg_column<T, U>);
+        case 2: return reinterpret_cast<const void *>(&k_pcg_column<T, 2 * U>);
+        case 3: return reinterpret_cast<const void *>(&k_pcg_column<T, 3 * U>);
+        case 4: return reinterpret_cast<const void *>(&k_pcg_column<T, 4 * U>);
+        default: return reinterpret_cast<const void *>(&k_pcg_column<T, 5 * U>);
+    }
+}
+
+// How a PC1 run of NR right-hand sides is launched: a launch per iteration, or
+// one persistent launch of tiles of r chunks, of a cell per thread or of a
+// column of cells per thread.
+enum RunKind { kRunLaunches = 0, kRunTiles = 1, kRunCells = 2, kRunColumns = 3 };
+
+// The kind of run (see MAS_LAUNCH_* in mas.h); MAS_EINVAL when the persistent
+// launch was asked for and is not possible.  Without a chunk length asked for,
+// the kinds that keep the grid in registers take it where it fits.
 template <typename T, int NR>
 static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
     if (cx.launch == MAS_LAUNCH_PER_ITERATION) return 0;
@@ -914,12 +956,13 @@ static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
     auto no = [&](const char *why) { return forced ? fail(MAS_EINVAL, "persistent launch: %s", why) : 0; };
     if (cx.timing) return no("sample_timing is set");
     const Shape &s = cx.op->s;
-    if (!forced && s.n > kPersistAutoCells) return 0;
+    const int planes = NR == 1 && cx.chunk == 0 && s.n > kSmallCells ? column_planes<T>(s) : 0;
+    if (!forced && s.n > kPersistAutoCells && !(planes > 0 && s.n > kColumnAutoCells)) return 0;
     const int V = iter_vec<T>(s.np, NR);
     const int64_t nblk = s.nblk_iter(V, persist_chunk(cx, V));
     int max_iter = iter0;
     for (int h = 0; h < NR; ++h) max_iter = std::max(max_iter, v.max_iter[h]);
-    if ((int64_t)(max_iter - iter0 + 1) * nblk >= ((int64_t)1 << 32))
+    if ((int64_t)(max_iter - iter0 + 1) * nblk >= ((int64_t)1 << 32))  // bounds the tags as well
         return no("max_iters too large for the barrier counter");
     int dev = 0, coop = 0, ncu = 0, per_cu = 0;
     HIPCHK(hipGetDevice(&dev));
@@ -929,11 +972,18 @@ static int persist_choice(Ctx &cx, const RhsSet<T> &v, int iter0) {
     if (cx.chunk == 0 && s.n <= kSmallCells) {
         HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&k_pcg_small<T, NR>),
                                                             kSmallThreads, 0));
-        if ((int64_t)per_cu * ncu >= small_blocks(s)) return 2;
+        if ((int64_t)per_cu * ncu >= small_blocks(s)) return kRunCells;
+    }
+    if constexpr (NR == 1) {
+        if (planes > 0) {
+            HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, column_kernel<T>(planes), kSmallThreads, 0));
+            if ((int64_t)per_cu * ncu >= column_blocks(s, planes)) return kRunColumns;
+        }
+        if (!forced && s.n > kPersistAutoCells) return kRunLaunches;
     }
     HIPCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persist_kernel<T, NR>(V, s.np), kWave * kTJ, 0));
     if ((int64_t)per_cu * ncu < nblk) return no("the iteration kernel's blocks do not fit on the GPU at once");
-    return 1;
+    return kRunTiles;
 }
 
 // Control blocks and counters of a PC1 run (one launch for all right-hand sides).
@@ -980,12 +1030,14 @@ static int persist_gave_up() {
                 kPersistWaitSec);
 }
 
-// A PC1 run of NR right-hand sides in one cooperative launch of
-// k_pcg_persist: the same control-block set-up, iterations, stopping and
-// results as run_pcg's launches per iteration, bit for bit.
+// A PC1 run of NR right-hand sides in one cooperative launch: the same
+// control-block set-up, iterations, stopping and results as run_pcg's launches
+// per iteration (tiles: bit for bit).  again, where given, is set with MAS_OK
+// when the launch failed, or a block gave up waiting, and nothing has changed
+// that another run starts from; without it that is MAS_EHIP.
 template <typename T, int NR>
 static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, int iter0,
-                           int check_every, bool cell_per_thread, PcgResult *res) {
+                           int check_every, RunKind kind, PcgResult *res, bool *again) {
     const mas_op *op = cx.op;
     const Shape &s = op->s;
     hipStream_t st = cx.stream;
@@ -999,7 +1051,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
     const uint64_t ticks = (uint64_t)((double)khz * 1000.0 * kPersistWaitSec);
-    if (work && cell_per_thread) {
+    if (work && kind != kRunTiles) {
         SmallArgs<T, NR> sa{};
         for (int h = 0; h < NR; ++h) {
             for (int t = 0; t < 2; ++t) {
@@ -1020,13 +1072,29 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         sa.rep = watch.rep;
         sa.d = s.dims();
         sa.nblk = (int)small_blocks(s);
+        const void *kernel = reinterpret_cast<const void *>(&k_pcg_small<T, NR>);
         sa.iter0 = iter0;
         sa.wait_ticks = ticks;
         void *args[] = {&sa};
-        HIPCHK(hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_pcg_small<T, NR>),
-                                          dim3((unsigned)sa.nblk), dim3(kSmallThreads), args, 0, st));
+        if constexpr (NR == 1) {
+            if (kind == kRunColumns) {
+                sa.ti = column_planes<T>(s);
+                sa.start_ticks = again ? (uint64_t)((double)khz * 1000.0 * kColumnStartSec) : ticks;
+                sa.nblk = (int)column_blocks(s, sa.ti);
+                kernel = column_kernel<T>(sa.ti);
+            }
+        }
+        const hipError_t le =
+            hipLaunchCooperativeKernel(kernel, dim3((unsigned)sa.nblk), dim3(kSmallThreads), args, 0, st);
+        if (le != hipSuccess && again) {
+            // nothing started (the cooperative queue may be another process's)
+            (void)hipGetLastError();
+            *again = true;
+            return MAS_OK;
+        }
+        HIPCHK(le);
     }
-    if (work && !cell_per_thread) {
+    if (work && kind == kRunTiles) {
         PersistArgs<T, NR> pa{};
         IterArgs<T> &a = pa.it;
         a.cr = c[0];
@@ -1064,10 +1132,21 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         HIPCHK(hipLaunchCooperativeKernel(persist_kernel<T, NR>(V, s.np), dim3((unsigned)a.nblk),
                                           dim3(kWave * kTJ), args, 0, st));
     }
-    // k_pcg_small leaves x complete
+    // the other kinds leave x complete
     int e = MAS_OK;
-    if (!cell_per_thread) e = launch_catchup<T, NR>(cx, v, iter0);
+    if (kind == kRunTiles) e = launch_catchup<T, NR>(cx, v, iter0);
     if (e != MAS_OK) return e;
+    auto gave_up = [&](const PersistSync &hs) {
+        if (!again || hs.done) return persist_gave_up();
+        *again = true;
+        return (int)MAS_OK;
+    };
+    PersistSync hs{};
+    auto read_sync = [&]() -> int {
+        HIPCHK(hipMemcpyAsync(&hs, cx.sync, sizeof hs, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
+        return MAS_OK;
+    };
     if (watch.rep.box && work) {
         e = wait_report(cx, [&] {
             watch.look();
@@ -1075,14 +1154,13 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         });
         if (e != MAS_OK) return e;
         if (!watch.stop) {
-            HIPCHK(hipStreamSynchronize(st));
-            return persist_gave_up();
+            e = read_sync();
+            return e != MAS_OK ? e : gave_up(hs);
         }
     } else {
-        PersistSync hs{};
-        HIPCHK(hipMemcpyAsync(&hs, cx.sync, sizeof hs, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        if (hs.err) return persist_gave_up();
+        e = read_sync();
+        if (e != MAS_OK) return e;
+        if (hs.err) return gave_up(hs);
         watch.rep.box = nullptr;  // no kernel ran, or none could report
     }
     return watch.finish(res);
@@ -1102,7 +1180,14 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
     {
         const int pc = persist_choice<T, NR>(cx, v, iter0);
         if (pc < 0) return pc;
-        if (pc > 0) return run_pcg_persist<T, NR>(cx, v, c, mode, iter0, check_every, pc == 2, res);
+        if (pc > 0) {
+            // a column run's blocks take whole CUs: where other kernels kept
+            // some from starting, the automatic choice launches per iteration
+            bool again = false;
+            const bool may = pc == kRunColumns && cx.launch != MAS_LAUNCH_PERSISTENT;
+            const int e = run_pcg_persist<T, NR>(cx, v, c, mode, iter0, check_every, (RunKind)pc, res, may ? &again : nullptr);
+            if (!again) return e;
+        }
     }
     cx.launched = MAS_LAUNCH_PER_ITERATION;
     const mas_op *op = cx.op;

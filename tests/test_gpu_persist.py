@@ -196,3 +196,42 @@ def test_cell_per_thread_matches_oracle(shape, precision):
                               allow_notconv=False)
     assert ora.rel_residual(b, to_host(X[0])) <= 1e-10 and ora.rel_residual(b, to_host(X[2])) <= 1e-10
     assert not X[1].any() and infos[2]["iters"] <= 1
+
+
+@pytest.mark.parametrize("precision,shape", [
+    ("fp64", (40, 57, 130)),    # a last tile of one row, one of two columns, 4 planes a block
+    ("fp64", (3, 250, 400)),    # one chunk, walls on both sides of it
+    ("fp64", (2300, 8, 15)),    # one tile holding the whole phi ring, 9 planes a block
+    ("fp64", (61, 127, 65)),    # a phi tile of one column, the last chunk shorter
+    ("fp64", (80, 128, 128)),   # every block and register: 10 planes
+    ("fp32_refined", (40, 57, 130)),
+    ("fp32_refined", (4100, 8, 8)),
+    ("fp32_refined", (157, 121, 125)),  # 20 planes
+])
+def test_column_per_thread_matches_oracle(shape, precision):
+    """A run with a column of cells per thread at the edges of its range, by the
+    automatic choice and asked for: the oracle's residual and its iterates, the
+    iteration counts of a launch per iteration, a warm start at the solution,
+    and the restarts of both refinements."""
+    p = problem(shape, (0, 1), q=1.0005 if shape[0] > 1000 else 1.02)
+    _, op = gpu_operator(p, precision)
+    ora = oracle_operator(p)
+    rhs, b = to_dev(p.rhs), ora.rhs_to_b(p.rhs)
+    o = dict(rtol=1e-10, precision=precision)
+    x, info = op.solve(rhs, S.make_opts(**o), allow_notconv=False)
+    assert info["launch"] == abi.MAS_LAUNCH_PERSISTENT
+    assert ora.rel_residual(b, to_host(x)) <= 1e-10
+    y, asked = op.solve(rhs, S.make_opts(launch="persistent", **o), allow_notconv=False)
+    assert torch.equal(x, y) and asked["iters"] == info["iters"]
+    y, per = op.solve(rhs, S.make_opts(launch="per_iteration", **o), allow_notconv=False)
+    assert per["launch"] == abi.MAS_LAUNCH_PER_ITERATION and abs(per["iters"] - info["iters"]) <= 1
+    y, warm = op.solve(rhs, S.make_opts(**o), x0=x.clone(), allow_notconv=False)
+    assert warm["iters"] <= 1 and ora.rel_residual(b, to_host(y)) <= 1e-10
+    if precision == "fp64":
+        for k in (1, 4):
+            y, _ = op.solve(rhs, S.make_opts(rtol=0.0, max_iters=k, max_restarts=0))
+            yo = ora.pcg(b, tol=0.0, max_iters=k)[0]
+            assert np.linalg.norm(to_host(y) - yo) <= 1e-11 * k * max(np.linalg.norm(yo), 1e-300)
+    else:
+        y, _ = op.solve(rhs, S.make_opts(refine="restart", **o), allow_notconv=False)
+        assert ora.rel_residual(b, to_host(y)) <= 1e-10
