@@ -1876,7 +1876,8 @@ __global__ void k_run_init(Ctl *ctl_all, PersistSync *sync, RunInit in) {
 }
 
 // ---------------------------------------------------------------- simple stencil tiles
-// Block (64, 4): 64 phi cells x 4 theta rows, looping over kSimpleR r planes.
+// Block (64, 4): 64 phi cells x 4 theta rows, looping over the r planes that
+// gridDim.z blocks share (at most kSimpleR each, see Shape::simple_grid).
 constexpr int kSimpleJ = 4;
 constexpr int kSimpleR = 16;
 constexpr int kSimpleNV = 3;  // most partial sums a simple-tile kernel writes per block
@@ -1891,8 +1892,9 @@ struct SimpleCell {
     {                                                                              \
         const int k_ = blockIdx.x * kWave + threadIdx.x;                           \
         const int j_ = blockIdx.y * kSimpleJ + threadIdx.y;                        \
-        const int ib_ = blockIdx.z * kSimpleR;                                     \
-        const int ie_ = min(ib_ + kSimpleR, (d).nr);                               \
+        const int per_ = ((d).nr + (int)gridDim.z - 1) / (int)gridDim.z;           \
+        const int ib_ = blockIdx.z * per_;                                         \
+        const int ie_ = min(ib_ + per_, (d).nr);                                   \
         const bool ok_ = (k_ < (d).np) && (j_ < (d).nt);                           \
         for (int i_ = ib_; i_ < ie_; ++i_) {                                       \
             SimpleCell cell{i_, j_, k_, ((int64_t)i_ * (d).nt + j_) * (d).np + k_, \

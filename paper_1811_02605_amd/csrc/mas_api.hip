@@ -234,9 +234,15 @@ struct Shape {
         const int last = np - (tiles_k(v) - 1) * seg(v);
         return v > 1 && last > v;
     }
+    // tiles of the elementwise kernels: kSimpleR planes a block, fewer where
+    // that leaves less than four blocks per CU (a block's planes follow one
+    // another, about 0.7 us each: 16 x 16 x 32 cells, 4 blocks of 16 planes or
+    // 64 of one, k_setup 13.1 and 6.2 us, k_unscale 6.8 and 3.0; 32 x 32 x 64: 16.2 and
+    // 7.5, 8.2 and 2.9)
     dim3 simple_grid() const {
-        return dim3((np + kWave - 1) / kWave, (nt + kSimpleJ - 1) / kSimpleJ,
-                    (nr + kSimpleR - 1) / kSimpleR);
+        const int64_t tiles = (int64_t)((np + kWave - 1) / kWave) * ((nt + kSimpleJ - 1) / kSimpleJ);
+        const int per = (int)std::min<int64_t>(kSimpleR, std::max<int64_t>(1, tiles * nr / (4 * kCUs)));
+        return dim3((np + kWave - 1) / kWave, (nt + kSimpleJ - 1) / kSimpleJ, (nr + per - 1) / per);
     }
     int64_t nblk_simple() const {
         dim3 g = simple_grid();

@@ -59,6 +59,21 @@ def test_apply_matches_oracle(shape, precision):
     assert rel(y, ora.apply(x)) <= 1e-13
 
 
+@pytest.mark.parametrize("shape", [(1031, 5, 3), (37, 130, 129), (40, 190, 300), (35, 257, 449)])
+def test_elementwise_tiles_of_few_planes(shape):
+    """The elementwise kernels with 2, 3, 8 and 12 r planes a block, the last
+    block with fewer: A x, and a solve (its norms, x scaled in and out)."""
+    p = problem(shape, (0, 1), q=1.001)
+    _, op = gpu_operator(p)
+    ora = oracle_operator(p)
+    x = np.random.default_rng(12).standard_normal(p.shape)
+    assert rel(to_host(op.apply(to_dev(x))), ora.apply(x)) <= 1e-13
+    y, info = op.solve(to_dev(p.rhs), S.make_opts(rtol=1e-10), allow_notconv=False)
+    b = ora.rhs_to_b(p.rhs)
+    assert abs(info["bnorm"] - np.linalg.norm(b)) <= 1e-12 * np.linalg.norm(b)
+    assert ora.rel_residual(b, to_host(y)) <= 1e-10
+
+
 # r planes per chunk of the iteration kernel: 0 is the automatic choice
 # (short chunks on these small grids, which cannot fill the GPU otherwise),
 # 16 and 18 the chunk lengths of grids large enough to fill it
