@@ -1222,11 +1222,14 @@ void k_pcg_iter(IterArgs<T> a) {
 // there, and a block starts iteration k + 1 only after every block has
 // finished iteration k, so no block overwrites what another still reads.
 struct PersistSync {
+    uint32_t start;  // arrivals at the first barrier, or kGaveUp (start_barrier)
     uint32_t bar;    // barrier arrivals, zero at launch
     int32_t err;     // 1: a block gave up waiting at a barrier
     int32_t done;    // 1: a block has finished the run (k_pcg_column)
     BlockCount count;
 };
+
+constexpr uint32_t kGaveUp = 0x80000000u;  // set in PersistSync::start
 
 template <typename T, int NR>
 struct PersistArgs {
@@ -1263,6 +1266,39 @@ __device__ inline bool grid_barrier(PersistSync *sync, uint32_t target, uint64_t
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         ok = good;
+    }
+    __syncthreads();
+    return ok != 0;
+}
+
+// A run's first barrier, by a word of its own that also decides, for all blocks
+// alike, whether every block is there: the first one to have waited too long
+// sets kGaveUp, which can be set only while some block has not arrived, and
+// every block that finds it set leaves.  (With a flag set after the wait a
+// block that arrives in between sees all arrivals and no flag, and waits for
+// the ones that have left at its next barrier.)  A wait of 0 gives up without
+// arriving.
+__device__ inline bool start_barrier(PersistSync *sync, uint32_t nblk, uint64_t wait_ticks) {
+    __shared__ int ok;
+    wait_stores();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t v = 0;  // at most nblk, far below kGaveUp, until given up
+        if (wait_ticks > 0) {
+            v = 1u + __hip_atomic_fetch_add(&sync->start, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t t0 = wall_clock64();
+            while (v < nblk && wall_clock64() - t0 <= wait_ticks) {
+                __builtin_amdgcn_s_sleep(1);
+                v = __hip_atomic_load(&sync->start, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        // a failed exchange has put the word's new value into v
+        while (v < nblk)
+            if (__hip_atomic_compare_exchange_strong(&sync->start, &v, v | kGaveUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT))
+                v |= kGaveUp;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        ok = (v & kGaveUp) == 0;
     }
     __syncthreads();
     return ok != 0;
@@ -1720,12 +1756,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_column(SmallArgs<T, 1> a)
         lS[t] = ok ? m * PL + l : 0;
         load(oS[t], rS[t], pS[t]);
     }
-    // every block runs once this one is passed; a block that starts after others
-    // have given up here finds err set
-    const bool here = grid_barrier(a.sync, (uint32_t)nblk, a.start_ticks);
-    if (tid == 0 && here && ld_agent(&a.sync->err)) gave_up = 1;
-    __syncthreads();
-    if (!here || gave_up) {
+    // every block runs once this one is passed, or none
+    if (!start_barrier(a.sync, (uint32_t)nblk, a.start_ticks)) {
         if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
         if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;

@@ -903,6 +903,13 @@ constexpr int64_t kColumnAutoCells = (int64_t)1 << 18;
 constexpr double kColumnStartSec = 0.004;
 constexpr double kPersistWaitSec = 2.0;
 
+// Not declared in mas.h: with it a test forces, from the host and for the calling
+// thread, the bounded waits of persistent runs (seconds; negative: the above).
+struct PersistWaits {
+    double start = -1.0, wait = -1.0;
+};
+static thread_local PersistWaits g_waits;
+
 // r planes per chunk of a persistent run (cx.chunk when set)
 static int persist_chunk(const Ctx &cx, int V) {
     if (cx.chunk > 0) return cx.chunk;
@@ -1056,7 +1063,10 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     int dev = 0, khz = 0;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
-    const uint64_t ticks = (uint64_t)((double)khz * 1000.0 * kPersistWaitSec);
+    auto ticks_of = [&](double forced, double sec) {
+        return (uint64_t)((double)khz * 1000.0 * (forced >= 0.0 ? forced : sec));
+    };
+    const uint64_t ticks = ticks_of(g_waits.wait, kPersistWaitSec);
     if (work && kind != kRunTiles) {
         SmallArgs<T, NR> sa{};
         for (int h = 0; h < NR; ++h) {
@@ -1085,7 +1095,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         if constexpr (NR == 1) {
             if (kind == kRunColumns) {
                 sa.ti = column_planes<T>(s);
-                sa.start_ticks = again ? (uint64_t)((double)khz * 1000.0 * kColumnStartSec) : ticks;
+                sa.start_ticks = ticks_of(g_waits.start, again ? kColumnStartSec : kPersistWaitSec);
                 sa.nblk = (int)column_blocks(s, sa.ti);
                 kernel = column_kernel<T>(sa.ti);
             }
@@ -2256,6 +2266,8 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
 }
 
 }  // namespace
+
+extern "C" void mas_test_persist_waits(double start, double wait) { g_waits = PersistWaits{start, wait}; }
 
 extern "C" int mas_pcg_solve(const mas_op *op, const double *rhs, double *x, const mas_pcg_opts *o,
                              void *work, int64_t work_bytes, void *hip_stream, mas_pcg_info *info) {

@@ -1,0 +1,83 @@
+"""Persistent runs whose blocks give up waiting.  The waits are bounded, so every
+block leaves normally; a test forces them short from the host, for its own
+thread."""
+import contextlib
+import ctypes
+import time
+
+import pytest
+import torch
+
+from gpu_util import gpu_operator, problem, to_dev
+from paper_1811_02605_amd import _abi as abi
+from paper_1811_02605_amd import solver as S
+
+pytestmark = pytest.mark.gpu
+
+
+@contextlib.contextmanager
+def waits(start=-1.0, wait=-1.0):
+    """Longest waits, in seconds, for all blocks to start and at an exchange
+    (negative: the library's own)."""
+    fn = abi.load().mas_test_persist_waits
+    fn.argtypes, fn.restype = [ctypes.c_double, ctypes.c_double], None
+    fn(start, wait)
+    try:
+        yield
+    finally:
+        fn(-1.0, -1.0)
+
+
+def close(a, b, rtol):
+    return float((a - b).norm() / b.norm()) <= rtol
+
+
+COLUMNS = (40, 57, 130)  # 0.3M cells
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+def test_columns_that_do_not_start_are_launched_per_iteration(precision):
+    p = problem(COLUMNS)
+    _, op = gpu_operator(p, precision)
+    rhs = to_dev(p.rhs)
+    o = dict(rtol=1e-10, precision=precision)
+    auto, per, asked = S.make_opts(**o), S.make_opts(launch="per_iteration", **o), S.make_opts(launch="persistent", **o)
+    ref, ri = op.solve(rhs, per)
+    x0 = (0.9 * ref).contiguous()
+    warm, wi = op.solve(rhs, per, x0=x0.clone())
+    lam, gnu, grhs, _ = op.adjoint(ref, rhs, per)
+    with waits(start=0.0):
+        x, info = op.solve(rhs, auto)
+        assert info["launch"] == abi.MAS_LAUNCH_PER_ITERATION and info["iters"] == ri["iters"]
+        assert torch.equal(x, ref)
+        x, info = op.solve(rhs, auto, x0=x0.clone())
+        assert info["iters"] == wi["iters"] and torch.equal(x, warm)
+        out = op.adjoint(ref, rhs, auto)
+        assert torch.equal(out[0], lam) and torch.equal(out[1], gnu) and torch.equal(out[2], grhs)
+        with pytest.raises(abi.MasError, match="waited more than"):
+            op.solve(rhs, asked)
+    x, info = op.solve(rhs, auto)
+    assert info["launch"] == abi.MAS_LAUNCH_PERSISTENT and close(x, ref, 1e-8)
+
+
+def test_blocks_give_up_starting_all_together():
+    """Start waits that follow the time that the blocks take to start, so that
+    about half are too short for the last ones.  All blocks then leave at once,
+    none waits 2 s for one that has left."""
+    p = problem(COLUMNS)
+    _, op = gpu_operator(p)
+    rhs = to_dev(p.rhs)
+    ref, _ = op.solve(rhs, S.make_opts(launch="per_iteration"))
+    o = S.make_opts()
+    op.solve(rhs, o)
+    us, launches = 20.0, {abi.MAS_LAUNCH_PER_ITERATION: 0, abi.MAS_LAUNCH_PERSISTENT: 0}
+    for _ in range(600):
+        with waits(start=us * 1e-6):
+            t0 = time.perf_counter()
+            x, info = op.solve(rhs, o)
+            dt = time.perf_counter() - t0
+        launches[info["launch"]] += 1
+        assert dt < 1.0, (us, dt)
+        assert close(x, ref, 1e-8), us
+        us *= 0.98 if info["launch"] == abi.MAS_LAUNCH_PERSISTENT else 1.02
+    assert min(launches.values()) > 50, launches
