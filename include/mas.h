@@ -142,7 +142,8 @@ typedef struct {
  *     starting for longer, the call returns MAS_EHIP instead of hanging.
  *   MAS_LAUNCH_AUTO: persistent where it is possible and the grid has at
  *     most 2^17 cells, or more than 2^18 and runs in columns; per iteration
- *     otherwise, and where other work keeps a run in columns from starting.
+ *     otherwise, and where other work keeps a run's blocks from starting (the
+ *     partial dot products are then summed in another order).
  * PC2 is always launched per iteration. */
 enum { MAS_LAUNCH_AUTO = 0, MAS_LAUNCH_PER_ITERATION = 1, MAS_LAUNCH_PERSISTENT = 2 };
 

@@ -1241,6 +1241,7 @@ struct PersistArgs {
     int iter0;                        // the run's first iteration index
     int keep_p[NR];                   // the first iteration continues the direction in p[c][iter0 & 1]
     uint64_t wait_ticks;              // longest wait at one barrier, in wall-clock ticks
+    uint64_t start_ticks;             // ... at the first one
 };
 
 // Grid barrier for co-resident blocks: the block's writes are released at
@@ -1336,7 +1337,10 @@ __global__ __launch_bounds__(kWave *WPB) void k_pcg_persist(PersistArgs<T, NR> a
         it.partials = a.partials[cur];
         it.xstep = (s >= 2 && (s & 1) == 0) ? 1 : 0;
         pcg_iter_body<T, NR, WPB, RPW, V, false, RAG>(it, sc);
-        if (!grid_barrier(a.sync, (uint32_t)(s + 1) * gridDim.x, a.wait_ticks)) {
+        // until the first one is passed nothing has changed that the run starts
+        // from: iteration iter0 leaves x alone and writes the other parity
+        if (s == 0 ? !start_barrier(a.sync, gridDim.x, a.start_ticks)
+                   : !grid_barrier(a.sync, (uint32_t)s * gridDim.x, a.wait_ticks)) {
             if (threadIdx.x == 0) {
                 __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (a.it.rep.box) put_host(&a.it.rep.box->waited, a.it.rep.token);
@@ -1434,7 +1438,7 @@ struct SmallArgs {
     int keep_p[NR];   // the first iteration continues the direction in p[c][iter0 & 1]
     uint64_t wait_ticks;
     int ti;           // k_pcg_column: r planes per block
-    uint64_t start_ticks;  // k_pcg_column: longest wait for every block to start
+    uint64_t start_ticks;  // longest wait for every block to start
 };
 
 // One exchange of a persistent run: the block's NV sums (acc: each thread's
@@ -1536,7 +1540,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
             x[h] = in ? a.x[h][cc] : T(0);
         }
     }
-    if (!grid_barrier(a.sync, (uint32_t)nblk, a.wait_ticks)) {
+    // only the slots have been written so far
+    if (!start_barrier(a.sync, (uint32_t)nblk, a.start_ticks)) {
         if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
         if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;

@@ -897,16 +897,24 @@ constexpr int64_t kPersistBlocks = 64;
 // shapes that fits was 1.23 (33 x 88 x 96, FP32) to 2.4 times faster so, also
 // with tiles of one column or row left over (79 x 65 x 129: 1.42 and 3.00 ms).
 constexpr int64_t kColumnAutoCells = (int64_t)1 << 18;
-// Its blocks need a CU each.  Where another process or stream keeps some of
-// them from starting for longer than this, the automatic choice launches per
-// iteration instead (a run of 1.2M cells takes 1.5 ms in columns, 3.4 ms so).
-constexpr double kColumnStartSec = 0.004;
+// The blocks of a persistent run must all be resident: in columns and with a
+// cell per thread they need up to a CU each.  Where another process or stream,
+// or a mask of the stream's CUs, keeps some of them from starting for longer
+// than this, the automatic choice launches per iteration instead, for the rest
+// of the call (a run of 1.2M cells takes 1.5 ms in columns, 3.4 ms so).  Matrix
+// products on another stream are no such work: beside products of 0.13 to 53 ms
+// each, of 192 runs (8K to 1.2M cells) one did not start in 4 ms, while launched
+// per iteration they take longer (8K cells beside 0.85 ms products 51 ms a solve,
+// 1.0 in one launch; 1.2M cells 86 and 5 ms); with 0.5 ms 7 of 12 did not.
+constexpr double kStartSec = 0.004;
 constexpr double kPersistWaitSec = 2.0;
 
 // Not declared in mas.h: with it a test forces, from the host and for the calling
 // thread, the bounded waits of persistent runs (seconds; negative: the above).
+// refuse: as if the runtime had refused the cooperative launch.
 struct PersistWaits {
     double start = -1.0, wait = -1.0;
+    bool refuse = false;
 };
 static thread_local PersistWaits g_waits;
 
@@ -1046,8 +1054,10 @@ static int persist_gave_up() {
 // A PC1 run of NR right-hand sides in one cooperative launch: the same
 // control-block set-up, iterations, stopping and results as run_pcg's launches
 // per iteration (tiles: bit for bit).  again, where given, is set with MAS_OK
-// when the launch failed, or a block gave up waiting, and nothing has changed
-// that another run starts from; without it that is MAS_EHIP.
+// when the launch failed, or blocks gave up waiting, and nothing has changed
+// that another run starts from; without it that is MAS_EHIP.  Nothing has if not
+// all blocks started, and until a block ends the run in k_pcg_column, which
+// keeps r, p and x in registers.
 template <typename T, int NR>
 static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, int iter0,
                            int check_every, RunKind kind, PcgResult *res, bool *again) {
@@ -1066,7 +1076,19 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
     auto ticks_of = [&](double forced, double sec) {
         return (uint64_t)((double)khz * 1000.0 * (forced >= 0.0 ? forced : sec));
     };
-    const uint64_t ticks = ticks_of(g_waits.wait, kPersistWaitSec);
+    const uint64_t ticks = ticks_of(g_waits.wait, kPersistWaitSec),
+                   start_ticks = ticks_of(g_waits.start, again ? kStartSec : kPersistWaitSec);
+    // false, with again set, where the launch was refused (the cooperative
+    // queue may be another process's): nothing has started then
+    hipError_t le = hipSuccess;
+    auto launch = [&](const void *kernel, int nblk, int threads, void **args) {
+        le = g_waits.refuse ? hipErrorLaunchFailure
+                            : hipLaunchCooperativeKernel(kernel, dim3((unsigned)nblk), dim3(threads), args, 0, st);
+        if (le == hipSuccess || !again) return true;
+        (void)hipGetLastError();
+        *again = true;
+        return false;
+    };
     if (work && kind != kRunTiles) {
         SmallArgs<T, NR> sa{};
         for (int h = 0; h < NR; ++h) {
@@ -1091,24 +1113,16 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         const void *kernel = reinterpret_cast<const void *>(&k_pcg_small<T, NR>);
         sa.iter0 = iter0;
         sa.wait_ticks = ticks;
+        sa.start_ticks = start_ticks;
         void *args[] = {&sa};
         if constexpr (NR == 1) {
             if (kind == kRunColumns) {
                 sa.ti = column_planes<T>(s);
-                sa.start_ticks = ticks_of(g_waits.start, again ? kColumnStartSec : kPersistWaitSec);
                 sa.nblk = (int)column_blocks(s, sa.ti);
                 kernel = column_kernel<T>(sa.ti);
             }
         }
-        const hipError_t le =
-            hipLaunchCooperativeKernel(kernel, dim3((unsigned)sa.nblk), dim3(kSmallThreads), args, 0, st);
-        if (le != hipSuccess && again) {
-            // nothing started (the cooperative queue may be another process's)
-            (void)hipGetLastError();
-            *again = true;
-            return MAS_OK;
-        }
-        HIPCHK(le);
+        if (!launch(kernel, sa.nblk, kSmallThreads, args)) return MAS_OK;
     }
     if (work && kind == kRunTiles) {
         PersistArgs<T, NR> pa{};
@@ -1144,16 +1158,18 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
         pa.sync = cx.sync;
         pa.iter0 = iter0;
         pa.wait_ticks = ticks;
+        pa.start_ticks = start_ticks;
         void *args[] = {&pa};
-        HIPCHK(hipLaunchCooperativeKernel(persist_kernel<T, NR>(V, s.np), dim3((unsigned)a.nblk),
-                                          dim3(kWave * kTJ), args, 0, st));
+        if (!launch(persist_kernel<T, NR>(V, s.np), a.nblk, kWave * kTJ, args)) return MAS_OK;
     }
+    if (le != hipSuccess) return fail(MAS_EHIP, "cooperative launch failed: %s", hipGetErrorString(le));
     // the other kinds leave x complete
     int e = MAS_OK;
     if (kind == kRunTiles) e = launch_catchup<T, NR>(cx, v, iter0);
     if (e != MAS_OK) return e;
     auto gave_up = [&](const PersistSync &hs) {
-        if (!again || hs.done) return persist_gave_up();
+        const bool unchanged = (hs.start & kGaveUp) != 0 || (kind == kRunColumns && !hs.done);
+        if (!again || !unchanged) return persist_gave_up();
         *again = true;
         return (int)MAS_OK;
     };
@@ -1197,12 +1213,13 @@ static int run_pcg(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int mode, i
         const int pc = persist_choice<T, NR>(cx, v, iter0);
         if (pc < 0) return pc;
         if (pc > 0) {
-            // a column run's blocks take whole CUs: where other kernels kept
-            // some from starting, the automatic choice launches per iteration
+            // where other work kept blocks from starting, the automatic choice
+            // launches per iteration, and does so for the rest of the call
             bool again = false;
-            const bool may = pc == kRunColumns && cx.launch != MAS_LAUNCH_PERSISTENT;
+            const bool may = cx.launch != MAS_LAUNCH_PERSISTENT;
             const int e = run_pcg_persist<T, NR>(cx, v, c, mode, iter0, check_every, (RunKind)pc, res, may ? &again : nullptr);
             if (!again) return e;
+            cx.launch = MAS_LAUNCH_PER_ITERATION;
         }
     }
     cx.launched = MAS_LAUNCH_PER_ITERATION;
@@ -2267,7 +2284,9 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
 
 }  // namespace
 
-extern "C" void mas_test_persist_waits(double start, double wait) { g_waits = PersistWaits{start, wait}; }
+extern "C" void mas_test_persist_waits(double start, double wait, int refuse) {
+    g_waits = PersistWaits{start, wait, refuse != 0};
+}
 
 extern "C" int mas_pcg_solve(const mas_op *op, const double *rhs, double *x, const mas_pcg_opts *o,
                              void *work, int64_t work_bytes, void *hip_stream, mas_pcg_info *info) {

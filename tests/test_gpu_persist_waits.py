@@ -16,37 +16,43 @@ pytestmark = pytest.mark.gpu
 
 
 @contextlib.contextmanager
-def waits(start=-1.0, wait=-1.0):
+def waits(start=-1.0, wait=-1.0, refuse=False):
     """Longest waits, in seconds, for all blocks to start and at an exchange
-    (negative: the library's own)."""
+    (negative: the library's own); or every cooperative launch refused."""
     fn = abi.load().mas_test_persist_waits
-    fn.argtypes, fn.restype = [ctypes.c_double, ctypes.c_double], None
-    fn(start, wait)
+    fn.argtypes, fn.restype = [ctypes.c_double, ctypes.c_double, ctypes.c_int], None
+    fn(start, wait, int(refuse))
     try:
         yield
     finally:
-        fn(-1.0, -1.0)
+        fn(-1.0, -1.0, 0)
 
 
 def close(a, b, rtol):
     return float((a - b).norm() / b.norm()) <= rtol
 
 
-COLUMNS = (40, 57, 130)  # 0.3M cells
+COLUMNS = ((40, 57, 130), 0)  # shape, chunk_planes: 0.3M cells, a column per thread
+CELLS = ((32, 32, 64), 0)  # a cell per thread
+TILES = ((32, 32, 64), 2)  # tiles of two r planes
+KINDS = [COLUMNS, CELLS, TILES]
+NOT_STARTED = [dict(start=0.0), dict(refuse=True)]
 
 
+@pytest.mark.parametrize("forced", NOT_STARTED)
 @pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
-def test_columns_that_do_not_start_are_launched_per_iteration(precision):
-    p = problem(COLUMNS)
+@pytest.mark.parametrize("shape,chunk", KINDS)
+def test_runs_that_do_not_start_are_launched_per_iteration(shape, chunk, precision, forced):
+    p = problem(shape)
     _, op = gpu_operator(p, precision)
     rhs = to_dev(p.rhs)
-    o = dict(rtol=1e-10, precision=precision)
+    o = dict(rtol=1e-10, precision=precision, chunk_planes=chunk)
     auto, per, asked = S.make_opts(**o), S.make_opts(launch="per_iteration", **o), S.make_opts(launch="persistent", **o)
     ref, ri = op.solve(rhs, per)
     x0 = (0.9 * ref).contiguous()
     warm, wi = op.solve(rhs, per, x0=x0.clone())
     lam, gnu, grhs, _ = op.adjoint(ref, rhs, per)
-    with waits(start=0.0):
+    with waits(**forced):
         x, info = op.solve(rhs, auto)
         assert info["launch"] == abi.MAS_LAUNCH_PER_ITERATION and info["iters"] == ri["iters"]
         assert torch.equal(x, ref)
@@ -54,21 +60,51 @@ def test_columns_that_do_not_start_are_launched_per_iteration(precision):
         assert info["iters"] == wi["iters"] and torch.equal(x, warm)
         out = op.adjoint(ref, rhs, auto)
         assert torch.equal(out[0], lam) and torch.equal(out[1], gnu) and torch.equal(out[2], grhs)
-        with pytest.raises(abi.MasError, match="waited more than"):
+        with pytest.raises(abi.MasError) as e:
             op.solve(rhs, asked)
+        assert e.value.status == abi.MAS_EHIP
     x, info = op.solve(rhs, auto)
     assert info["launch"] == abi.MAS_LAUNCH_PERSISTENT and close(x, ref, 1e-8)
 
 
-def test_blocks_give_up_starting_all_together():
-    """Start waits that follow the time that the blocks take to start, so that
-    about half are too short for the last ones.  All blocks then leave at once,
-    none waits 2 s for one that has left."""
-    p = problem(COLUMNS)
+@pytest.mark.parametrize("forced", NOT_STARTED)
+@pytest.mark.parametrize("precision", ["fp64", "fp32_refined"])
+@pytest.mark.parametrize("shape,chunk", [CELLS, TILES])
+def test_several_rhs_that_do_not_start(shape, chunk, precision, forced):
+    p = problem(shape)
+    _, op = gpu_operator(p, precision)
+    rhs = to_dev(p.rhs)
+    b = torch.stack([rhs, torch.zeros_like(rhs), rhs.flip(2)])
+    o = dict(rtol=1e-10, precision=precision, chunk_planes=chunk)
+    ref, ri = op.solve_multi(b, S.make_opts(launch="per_iteration", **o))
+    with waits(**forced):
+        x, info = op.solve_multi(b, S.make_opts(**o))
+    assert torch.equal(x, ref)
+    for h in range(3):
+        assert info[h]["launch"] == abi.MAS_LAUNCH_PER_ITERATION and info[h]["iters"] == ri[h]["iters"]
+
+
+def test_allocation_free_solve_that_does_not_start():
+    p = problem("c0")
     _, op = gpu_operator(p)
     rhs = to_dev(p.rhs)
     ref, _ = op.solve(rhs, S.make_opts(launch="per_iteration"))
-    o = S.make_opts()
+    for forced in NOT_STARTED:
+        with waits(**forced):
+            x, info = op.solve_noalloc(rhs, S.make_opts())
+        assert info["launch"] == abi.MAS_LAUNCH_PER_ITERATION and torch.equal(x, ref)
+
+
+@pytest.mark.parametrize("shape,chunk", KINDS)
+def test_blocks_give_up_starting_all_together(shape, chunk):
+    """Start waits that follow the time that the blocks take to start, so that
+    about half are too short for the last ones.  All blocks then leave at once,
+    none waits 2 s for one that has left."""
+    p = problem(shape)
+    _, op = gpu_operator(p)
+    rhs = to_dev(p.rhs)
+    ref, _ = op.solve(rhs, S.make_opts(launch="per_iteration"))
+    o = S.make_opts(chunk_planes=chunk)
     op.solve(rhs, o)
     us, launches = 20.0, {abi.MAS_LAUNCH_PER_ITERATION: 0, abi.MAS_LAUNCH_PERSISTENT: 0}
     for _ in range(600):
