@@ -662,6 +662,7 @@ struct Ctx {
     PersistSync *sync = nullptr;     // barrier words of the persistent launch
     int launch = MAS_LAUNCH_AUTO;    // requested launch mode of PC1 runs
     int launched = 0;                // mode of the last PC1 run (0: none yet)
+    uint32_t ended = 0;              // token of a persistent run that has reported its end (check_ended)
     // event samples of the iteration kernel
     std::vector<hipEvent_t> ev;
     std::vector<int> ev_iter;
@@ -709,6 +710,29 @@ static int begin_call(Ctx &cx) {
     return MAS_OK;
 }
 
+constexpr double kPersistWaitSec = 2.0;
+
+static int persist_gave_up() {
+    return fail(MAS_EHIP, "persistent PCG run: a block waited more than %g s at a grid barrier",
+                kPersistWaitSec);
+}
+
+// One block reports the end of a persistent run, while another may have given up
+// at its last exchange and left its part of x as it was.  The run's launch has
+// ended when this is called, after the next wait for the stream.
+static int check_ended(Ctx &cx) {
+    if (cx.ended == 0u) return MAS_OK;
+    const uint32_t token = cx.ended;
+    cx.ended = 0u;
+    return __atomic_load_n(&cx.box->waited, __ATOMIC_ACQUIRE) == token ? persist_gave_up() : MAS_OK;
+}
+
+// Everything queued by a call has ended.
+static int end_call(Ctx &cx) {
+    HIPCHK(hipStreamSynchronize(cx.stream));
+    return check_ended(cx);
+}
+
 // Sums a kernel has formed (finish_sums) under report rep.
 static int get_sums(Ctx &cx, Report rep, int nv, double *out) {
     if (!rep.box) {
@@ -720,7 +744,7 @@ static int get_sums(Ctx &cx, Report rep, int nv, double *out) {
     const int e = wait_report(cx, [&] { return __atomic_load_n(&rep.box->sums_done, __ATOMIC_ACQUIRE) == rep.token; });
     if (e != MAS_OK) return e;
     for (int t = 0; t < nv; ++t) out[t] = rep.box->sums[t];
-    return MAS_OK;
+    return check_ended(cx);
 }
 
 struct PcgResult {
@@ -907,7 +931,6 @@ constexpr int64_t kColumnAutoCells = (int64_t)1 << 18;
 // per iteration they take longer (8K cells beside 0.85 ms products 51 ms a solve,
 // 1.0 in one launch; 1.2M cells 86 and 5 ms); with 0.5 ms 7 of 12 did not.
 constexpr double kStartSec = 0.004;
-constexpr double kPersistWaitSec = 2.0;
 
 // Not declared in mas.h: with it a test forces, from the host and for the calling
 // thread, the bounded waits of persistent runs (seconds; negative: the above).
@@ -1044,11 +1067,6 @@ static void launch_iter(const IterArgs<T> &a, bool halo, int V, hipStream_t st) 
         halo ? go(IW{}, Tr{}, Tr{}) : go(IW{}, F{}, Tr{});
     else
         halo ? go(IW{}, Tr{}, F{}) : go(IW{}, F{}, F{});
-}
-
-static int persist_gave_up() {
-    return fail(MAS_EHIP, "persistent PCG run: a block waited more than %g s at a grid barrier",
-                kPersistWaitSec);
 }
 
 // A PC1 run of NR right-hand sides in one cooperative launch: the same
@@ -1189,6 +1207,7 @@ static int run_pcg_persist(Ctx &cx, const RhsSet<T> &v, const T *const c[3], int
             e = read_sync();
             return e != MAS_OK ? e : gave_up(hs);
         }
+        cx.ended = watch.rep.token;
     } else {
         e = read_sync();
         if (e != MAS_OK) return e;
@@ -1819,7 +1838,8 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
 
     hipLaunchKernelGGL(k_unscale, sgrid, sblock, 0, cx.stream, op->w, d, x);
     LAUNCHCHK();
-    HIPCHK(hipStreamSynchronize(cx.stream));
+    st = end_call(cx);
+    if (st != MAS_OK) return st;
     info.status = status;
     info.launch = cx.launched;
     info.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -2040,7 +2060,8 @@ static int solve_multi_core(const mas_op *op, const double *rhs, double *x, cons
         if (info[h].status == MAS_EBREAKDOWN) status = MAS_EBREAKDOWN;
         else if (info[h].status == MAS_ENOTCONV && status == MAS_OK) status = MAS_ENOTCONV;
     }
-    HIPCHK(hipStreamSynchronize(stream));
+    const int ended = end_call(cx);
+    if (ended != MAS_OK) return ended;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     for (int h = 0; h < NR; ++h) {
         info[h].seconds = secs;
@@ -2273,7 +2294,8 @@ static int solve_multi_refined(const mas_op *op, const double *rhs, double *x,
         if (info[h].status == MAS_EBREAKDOWN) status = MAS_EBREAKDOWN;
         else if (info[h].status == MAS_ENOTCONV && status == MAS_OK) status = MAS_ENOTCONV;
     }
-    HIPCHK(hipStreamSynchronize(stream));
+    const int ended = end_call(cx);
+    if (ended != MAS_OK) return ended;
     const double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     for (int h = 0; h < NR; ++h) {
         info[h].seconds = secs;

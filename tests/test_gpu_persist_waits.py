@@ -4,6 +4,7 @@ thread."""
 import contextlib
 import ctypes
 import time
+import warnings
 
 import pytest
 import torch
@@ -117,3 +118,30 @@ def test_blocks_give_up_starting_all_together(shape, chunk):
         assert close(x, ref, 1e-8), us
         us *= 0.98 if info["launch"] == abi.MAS_LAUNCH_PERSISTENT else 1.02
     assert min(launches.values()) > 50, launches
+
+
+@pytest.mark.parametrize("iters", [1, 2])
+@pytest.mark.parametrize("shape", [(9, 16, 32), (32, 32, 64), (40, 57, 130)])
+def test_a_block_that_gives_up_last_is_not_missed(shape, iters):
+    """Exchange waits that follow the time an exchange takes, so that in about half
+    of the calls some blocks give up, also at the run's last exchange where others
+    end it.  A call then fails; one that does not has every cell of x."""
+    p = problem(shape)
+    _, op = gpu_operator(p)
+    rhs = to_dev(p.rhs)
+    o = S.make_opts(rtol=0.0, max_iters=iters, max_restarts=0, launch="persistent")
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")  # not converged
+        ref, _ = op.solve(rhs, o)
+        us, failed, n = 10.0, 0, 1500
+        for _ in range(n):
+            try:
+                with waits(wait=us * 1e-6):
+                    x, _ = op.solve(rhs, o)
+                assert torch.equal(x, ref), us
+                us *= 0.99
+            except abi.MasError as e:
+                assert e.status == abi.MAS_EHIP
+                failed += 1
+                us *= 1.01
+    assert 100 < failed < n - 100
