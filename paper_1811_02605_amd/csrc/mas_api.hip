@@ -666,7 +666,9 @@ struct Ctx {
     // event samples of the iteration kernel
     std::vector<hipEvent_t> ev;
     std::vector<int> ev_iter;
+    bool queued = false;  // kernels may be under way: no return of the call leaves any
     ~Ctx() {
+        if (queued) (void)hipStreamSynchronize(stream);
         for (auto e : ev) (void)hipEventDestroy(e);
     }
 };
@@ -705,6 +707,7 @@ static int begin_call(Ctx &cx) {
         const int e = pinned_box(&cx.box);
         if (e != MAS_OK) return e;
     }
+    cx.queued = true;
     hipLaunchKernelGGL(k_run_init, dim3(1), dim3(256), 0, cx.stream, cx.ctl, cx.sync, RunInit{});
     LAUNCHCHK();
     return MAS_OK;
@@ -730,6 +733,7 @@ static int check_ended(Ctx &cx) {
 // Everything queued by a call has ended.
 static int end_call(Ctx &cx) {
     HIPCHK(hipStreamSynchronize(cx.stream));
+    cx.queued = false;
     return check_ended(cx);
 }
 
@@ -1580,7 +1584,8 @@ static int solve_core(const mas_op *op, const double *src, int src_is_rhs, doubl
     if (bnorm == 0.0) {
         hipLaunchKernelGGL(k_fill<double>, sgrid, sblock, 0, cx.stream, x, d, 0.0);
         LAUNCHCHK();
-        HIPCHK(hipStreamSynchronize(cx.stream));
+        st = end_call(cx);
+        if (st != MAS_OK) return st;
         info.status = MAS_OK;
         info.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         if (info_out) *info_out = info;
