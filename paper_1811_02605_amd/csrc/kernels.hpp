@@ -172,6 +172,14 @@ __device__ inline void block_sum_store(double (&v)[NV], double *out, int64_t nbl
 // Wait until this wave's stores have been acknowledged.
 __device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// What one lane of a wave has written to LDS, for the other lanes of that wave:
+// orders the accesses for the compiler (the wave's LDS accesses run in order).
+__device__ inline void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Counters of the blocks of a launch that have finished: kCountGroups groups of
 // blocks count in lines of their own and the last block of each group counts
 // in the first line.  Additions to one line take turns: with one counter for
@@ -1858,6 +1866,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_column(SmallArgs<T, 1> a)
             for (int u = 0; u < kSmallBlocks / kWave; ++u) S[t] += sAll[u][t];
         }
         if (lane == 0) pcg_finalize(&lc, S);
+        wave_fence();
     }
     if (tid == 0) st_agent(&a.sync->done, 1);
 #pragma unroll
