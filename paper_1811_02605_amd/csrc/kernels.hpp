@@ -1449,12 +1449,23 @@ struct SmallArgs {
     uint64_t start_ticks;  // longest wait for every block to start
 };
 
+// Places the code that follows at PHASE dwords past a multiple of 32 bytes.  The
+// time of k_pcg_small's loops depends on where their eight-byte instructions lie:
+// 64 x 32 x 64 cells 946 us a solve with both at phase 4, 976 to 1134 where the
+// code before them happened to put them (950 to 1059 by the outer loop's phase);
+// k_pcg_column's exchange is the same within 0.5%.
+template <int PHASE>
+__device__ __forceinline__ void align_code() {
+    asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(PHASE));
+}
+
 // One exchange of a persistent run: the block's NV sums (acc: each thread's
 // part) become words tagged with the iteration's number, once everything the
 // block has published before is acknowledged; then every block's words are
 // read until their tags match, and sAll holds each wave's part of the totals.
 // False (for the whole block) once a wait exceeds wait_ticks.
-template <int NV>
+// PHASE: see align_code.
+template <int NV, int PHASE>
 __device__ __forceinline__ bool exchange_sums(double (&acc)[NV], double (*sWave)[NV], double (*sAll)[NV],
                                               int *gave_up, uint64_t *slots, int nblk, int blk, uint32_t tag,
                                               uint64_t wait_ticks) {
@@ -1483,6 +1494,7 @@ __device__ __forceinline__ bool exchange_sums(double (&acc)[NV], double (*sWave)
         if (tid < nblk) {
             const uint64_t t0 = wall_clock64();
             for (;;) {
+                align_code<PHASE>();
                 uint64_t g[2 * NV];
 #pragma unroll
                 for (int t = 0; t < 2 * NV; ++t) g[t] = ld_agent(slots + (int64_t)t * nblk + tid);
@@ -1560,6 +1572,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
         else return sCtl[h];
     };
     for (int k = a.iter0;; ++k) {
+        align_code<4>();
         const int cur = k & 1, nxt = cur ^ 1, s = k - a.iter0;
         double acc[NV];
 #pragma unroll
@@ -1598,8 +1611,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
                 acc[h * kNV + 4] = t * t;
             }
         }
-        const bool done = exchange_sums<NV>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk, nblk,
-                                            blk, (uint32_t)s + 1u, a.wait_ticks);
+        const bool done = exchange_sums<NV, 4>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk,
+                                               nblk, blk, (uint32_t)s + 1u, a.wait_ticks);
         if (!done) {
             if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
             if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1851,8 +1864,8 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_column(SmallArgs<T, 1> a)
                 acc[4] += t * t;
             }
         }
-        const bool done = exchange_sums<NV>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk, nblk,
-                                            blk, (uint32_t)s + 1u, a.wait_ticks);
+        const bool done = exchange_sums<NV, 0>(acc, sWave, sAll, &gave_up, a.slots + (int64_t)cur * (2 * NV) * nblk,
+                                               nblk, blk, (uint32_t)s + 1u, a.wait_ticks);
         if (!done) {
             if (tid == 0 && a.rep.box) put_host(&a.rep.box->waited, a.rep.token);
             if (tid == 0) __hip_atomic_store(&a.sync->err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
