@@ -636,7 +636,9 @@ static thread_local Pinned g_pinned;
 static int pinned_box(HostBox **out) {
     if (!g_pinned.p) {
         void *p = nullptr;
-        HIPCHK(hipHostMalloc(&p, sizeof(HostBox), hipHostMallocCoherent));
+        // every device that this thread comes to use writes into it
+        HIPCHK(hipHostMalloc(&p, sizeof(HostBox),
+                             hipHostMallocCoherent | hipHostMallocPortable | hipHostMallocMapped));
         std::memset(p, 0, sizeof(HostBox));
         g_pinned.p = static_cast<HostBox *>(p);
     }
