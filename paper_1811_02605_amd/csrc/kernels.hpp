@@ -192,9 +192,8 @@ struct BlockCount {
 
 // Whether this block is the last of nblk to come here, uniform across the
 // block (blk: its index).  What the block's first wave has stored at agent
-// scope before is then
-// visible, for the last block, to agent-scope loads: the wave waits until its
-// stores have been acknowledged before it counts itself (relaxed: a release
+// scope before is then visible, for the last block, to agent-scope loads: the
+// wave waits until its stores have been acknowledged before it counts itself (relaxed: a release
 // would write back the whole L2, which cost the iteration kernel 17% on the
 // 52.4M-cell grid).  The counters are zero before the launch and after it.
 __device__ inline bool last_block(BlockCount *count, uint32_t nblk, uint32_t blk) {
@@ -264,10 +263,10 @@ __device__ inline void report_ctl(Report rep, int c, const Ctl *ctl) {
 }
 
 // ---------------------------------------------------------------- CG finalize
-// Fixed-order sum of NV of the partials (values 0, VS, 2 VS, ... of [][nblk]) over nblk blocks by the NT threads of one block, read
-// at agent scope: thread t adds blocks t, t + NT, ... in order, the waves
-// combine by a butterfly, the wave sums are added in wave order (bitwise
-// reproducible).  Every thread gets the sums.  kSumAhead blocks' partials are
+// Fixed-order sum of NV of the partials (values 0, VS, 2 VS, ... of [][nblk])
+// over nblk blocks by the NT threads of one block, read at agent scope: thread t
+// adds blocks t, t + NT, ... in order, each wave adds its lanes by wave_sum, the
+// wave sums are added in wave order (bitwise reproducible).  Every thread gets the sums.  kSumAhead blocks' partials are
 // loaded before they are added: the loads miss every cache on the way (one at
 // a time, the persistent run on 32 x 32 x 64 cells took 12.8 instead of 10.6 us
 // per iteration).
@@ -379,7 +378,7 @@ __device__ inline void pcg_finalize(Ctl *ctl, const double (&S)[kNV]) {
     }
 }
 
-// The NV sums over all blocks' partials ([nblk][NV]), by the last block of a
+// The NV sums over all blocks' partials ([NV][nblk]), by the last block of a
 // kernel with NT threads: to the host, and to the control block.
 template <int NT, int NV>
 __device__ inline void finish_sums(const double *partials, int nblk, int blk, BlockCount *count, Ctl *ctl,
@@ -1426,8 +1425,8 @@ __global__ __launch_bounds__(256) void k_x_catchup(CatchupArgs<T> a) {
 // writes a slot again only after every block has published the iteration
 // between, and so has read it.  The slots are cleared, behind one barrier with
 // a counter, before the first iteration.  Waits are bounded as in grid_barrier.
-// 32 x 32 x 64 cells: 6.0 us an iteration, 9.6 with tiles and their vectors in
-// memory (k_pcg_persist); 16 x 16 x 32 cells 4.0 and 7.6.
+// 32 x 32 x 64 cells: 6.4 us an iteration, 9.4 with tiles and their vectors in
+// memory (k_pcg_persist); 16 x 16 x 32 cells 4.3 and 7.7.
 constexpr int kSmallThreads = 512;  // 1024: 2-20% slower
 constexpr int64_t kSmallCells = (int64_t)1 << 17;
 constexpr int kSmallBlocks = (int)(kSmallCells / kSmallThreads);  // one thread polls each block
@@ -1666,7 +1665,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pcg_small(SmallArgs<T, NR> a)
 // What is left is the exchange (8-9 us) and, per plane, 0.4 us.  us per
 // iteration, launched per iteration in brackets: 64 x 96 x 192 cells 14.2
 // (31.1), FP32 13.6 (24.1); 33 x 88 x 96 11.4 (16.7); 80 x 128 x 128 13.9
-// (32.9); FP32 160 x 128 x 128, whose 20 planes spill 55 registers, 21.4 (32.6).
+// (32.9); FP32 160 x 128 x 128, whose 20 planes spill 57 registers, 21.4 (32.6).
 // r, p and x reach memory only at the end of a run that ends regularly: a run
 // that gave up has changed nothing but q, and can be made in another way, if
 // no block has set sync->done.

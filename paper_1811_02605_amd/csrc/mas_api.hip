@@ -53,7 +53,7 @@ static int fail(int status, const char *fmt, ...) {
 // ------------------------------------------------------------------ tile configuration
 // Iteration kernel: (64 V) phi cells x kTJ theta rows (one wave each) per
 // block, an r chunk of Shape::ti() planes per block; V = 16 bytes / element
-// size when np is a multiple of it, else 1.
+// size, 1 where a row is shorter than that.
 #ifndef MAS_TJ
 #define MAS_TJ 4
 #endif
@@ -945,11 +945,16 @@ static int launch_catchup(Ctx &cx, const RhsSet<T> &v, int iter0) {
 // A block gives up waiting at a grid barrier after kPersistWaitSec seconds.
 constexpr int64_t kPersistAutoCells = (int64_t)1 << 17;
 constexpr int64_t kPersistBlocks = 64;
-// Above that, a grid of up to 2^18 cells is launched per iteration by the
-// automatic choice, as callers may rely on; a larger one runs in columns where
-// it fits (FP64 up to 1.3M cells, FP32 2.6M, with full tiles).  Every one of 11
-// shapes that fits was 1.23 (33 x 88 x 96, FP32) to 2.4 times faster so, also
-// with tiles of one column or row left over (79 x 65 x 129: 1.42 and 3.00 ms).
+// Above kColumnAutoCells a grid runs in columns where it fits (FP64 up to 1.3M
+// cells, FP32 2.6M, with full tiles).  Every one of 11 shapes that fits was 1.23
+// (33 x 88 x 96, FP32) to 2.4 times faster so, also with tiles of one column or
+// row left over (79 x 65 x 129: 1.42 and 3.00 ms).  The line is no crossover:
+// between kPersistAutoCells and it columns are faster too, asked for explicitly
+// (ms a solve, launched per iteration in brackets: 34 x 50 x 79 cells 0.97 (1.46),
+// FP32 1.11 (1.45); 20 x 90 x 140 1.30 (1.96), FP32 1.30 (1.77); 32 x 64 x 128
+// 1.10 (1.78), FP32 1.20 (1.54)).  It lies at 2^18 because the automatic choice
+// has promised launches per iteration (mas_pcg_info.launch) just above 2^17 cells
+// from before there were columns, and 32 x 64 x 128 cells are held to that.
 constexpr int64_t kColumnAutoCells = (int64_t)1 << 18;
 // The blocks of a persistent run must all be resident: in columns and with a
 // cell per thread they need up to a CU each.  Where another process or stream,

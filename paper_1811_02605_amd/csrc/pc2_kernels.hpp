@@ -267,9 +267,11 @@ __global__ __launch_bounds__(kWave) void k_pc2_factor(Pc2FacArgs a, TOUT *dout) 
 // that the forward sweep of the plane above read too.
 // Right-hand sides run one after the other on the same coefficients; in single
 // precision the next one's r and q are in flight while one is swept.  In
-// double precision those 32 registers spill (four waves per SIMD, so that two
-// blocks share a CU: one loads while the other sweeps): three right-hand
-// sides on 256 x 320 x 640 cells 164 ms a solve with them, 122 ms without.
+// double precision those 32 registers more spill (four waves per SIMD, so that
+// two blocks share a CU: one loads while the other sweeps): three right-hand
+// sides on 256 x 320 x 640 cells 164 ms a solve with them, 122 ms without.  Two,
+// three and four right-hand sides in double precision spill 10, 16 and 29
+// registers all the same, four in single precision 13.
 // 256 x 320 x 640 cells, one right-hand side: 670 us in double precision (5.6
 // TB/s at 72 B per cell) and 360 us in single (40 B), against 1340 and 735 us
 // for one wave per block that walked the 64 rows alone, re-read the
